@@ -46,6 +46,20 @@ inline void geom_blocked(Geom& g)
     }
 }
 
+// The same with B = 16 for rows that 16 does not divide: the last chunk of a
+// row is only partly used, so that every run of 16 nodes starts on a 128-byte
+// line in FP64.
+inline void geom_blocked16(Geom& g)
+{
+    const uint32_t chunks = (g.nx + 15) / 16;
+    g.plane = 16;
+    g.chunk = 27 * 16;
+    g.row = g.chunk * chunks;
+    g.slab = g.row * g.ny;
+    g.xshift = 4;
+    g.xmask = 15;
+}
+
 inline bool geom_is_planes(const Geom& g) { return g.row == g.nx && g.xshift == 31 && g.plane >= g.nnodes; }
 
 // Elements of the buffer that the layout spans.
@@ -69,6 +83,88 @@ hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, co
 using StepFn = void (*)(StepParams);
 hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gamma, const Geom& g,
                              StepFn* fn, uint32_t* grid, uint32_t* block);
+
+// ---------------------------------------------------------------------------
+// Two steps of a pull box in one launch (k_pair, kbc_pair.h): a workgroup of
+// kPairBlock threads owns a tile of tx x ty columns and lz planes.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kPairBlock = 256;   // (tx + 2)(ty + 2), at most
+constexpr uint32_t kPairInner = 192;   // tx ty, at most (three whole waves)
+
+struct PairTiles {
+    uint32_t tx, ty;     // columns of a tile
+    uint32_t ntx, nty;   // tiles along x and y
+    uint32_t lz;         // planes of a tile (the last one along z may have fewer)
+    uint32_t grid;       // workgroups
+};
+
+// Waves per SIMD of k_pair: two by registers and LDS in FP64, three in FP32.
+constexpr uint32_t pair_waves(int storage) { return storage == ST_F64 ? 2 : 3; }
+
+// Whether a pull box takes its steps in pairs, and with which tiles.
+//
+// A tile row is one 128-byte line: narrower or unaligned rows make the
+// non-temporal stores partial lines, and the sweep runs 1.6-2.3x slower
+// (tiles 18, 20, 22 or 30 wide at 256^3).  16 x 12 in FP64 keeps 192 of the
+// 252 nodes computed per plane.
+//
+// lz minimises plane iterations of the whole GPU, measured as rounds of
+// resident workgroups times lz + 2 (a tile computes two planes more than it
+// stores).  A last round that leaves half the slots empty runs its planes in
+// 0.68 of the time.  Over cubes of 64-256 nodes the choice is the fastest of
+// the measured lz or within 2% of it, except 6% at 240.
+//
+// `fill` is the share of the plane iterations' node capacity that the box
+// uses.  FP64, natural s, pairs against single steps: 48^3 (0.33) 0.87x,
+// 64^3 (0.44) 1.18x, 80^3 (0.65) 1.13x, 128^3 (0.76) 1.20x, 256^3 (0.88)
+// 1.45x; central s, whose extra arithmetic is no longer hidden, 128^3 1.09x,
+// 256^3 1.31x.  FP32 (32 x 5 tiles, more of the sweep is arithmetic):
+// 128^3 (0.66) 1.00x, 160^3 (0.76) 1.10x, 192^3 1.12x, 256^3 (0.86) 1.26x;
+// central 256^3 1.05x.  FP32 with the FP64-formed non-equilibrium ran 0.97x
+// at 256^3 and FP16 is bound by arithmetic, so they keep single steps, as
+// does the exact stabilizer.
+inline bool pair_plan(int storage, int variant, bool exact_gamma, const Geom& g, uint32_t cus,
+                      PairTiles* out)
+{
+    if (exact_gamma || (storage != ST_F64 && storage != ST_F32)) return false;
+    if (storage == ST_F32 && (is_central(variant) || g.nx % 32)) return false;
+    PairTiles p;
+    p.tx = storage == ST_F64 ? 16 : 32;
+    p.ty = storage == ST_F64 ? 12 : 5;
+    p.ntx = (g.nx + p.tx - 1) / p.tx;
+    p.nty = (g.ny + p.ty - 1) / p.ty;
+    const double slots = (double)cus * pair_waves(storage);
+    const double tiles = (double)p.ntx * p.nty;
+    double best = 0.0;
+    p.lz = 0;
+    for (uint32_t chunks = 1; chunks <= g.nz && chunks <= 64; ++chunks) {
+        const uint32_t lz = (g.nz + chunks - 1) / chunks;
+        const double w = tiles * ((g.nz + lz - 1) / lz) / slots;
+        const double whole = (double)(uint64_t)w, part = w - whole;
+        const double cost = (whole + (part == 0.0 ? 0.0 : (part <= 0.5 ? 0.68 : 1.0))) * (lz + 2);
+        if (p.lz == 0 || cost < best) {
+            best = cost;
+            p.lz = lz;
+        }
+    }
+    const double fill = (double)g.nnodes / (best * slots * p.tx * p.ty);
+    const double least = storage == ST_F32 ? 0.72 : (is_central(variant) ? 0.6 : 0.42);
+    if (fill < least) return false;
+    p.grid = p.ntx * p.nty * ((g.nz + p.lz - 1) / p.lz);
+    *out = p;
+    return true;
+}
+
+struct PairParams {
+    const void* src;
+    void* dst;
+    Geom g;
+    Coll c;
+    PairTiles p;
+};
+using PairFn = void (*)(PairParams);
+// The kernel pair_plan's boxes run (storage FP64 or FP32 dev).
+PairFn pair_step(int storage, int variant);
 
 // Write f^eq(rho, u) of device fields u [3][N], rho [N] (may be NULL) into the
 // storage buffer in the given layout.
@@ -202,6 +298,8 @@ using GammaFn = void (*)(int, const void*, Geom, Coll, LoadCtx, double*);
 // take a kernel with that geometry compiled in)
 template <int S, bool GX>
 StepFn step_kernel(int variant, int sweep, bool c64);
+template <int S>
+PairFn pair_kernel(int variant);               // FP64 and FP32 dev, estimate gamma only
 template <int S>
 PoolFn pool_kernel(int variant, int sweep, bool one);   // estimate gamma only
 template <int S, bool GX>

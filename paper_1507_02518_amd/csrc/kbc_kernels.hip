@@ -587,6 +587,11 @@ hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, co
     return hipGetLastError();
 }
 
+PairFn pair_step(int storage, int variant)
+{
+    return storage == ST_F64 ? pair_kernel<ST_F64>(variant) : pair_kernel<ST_F32>(variant);
+}
+
 hipError_t launch_pool_step(int storage, int variant, int sweep, const PoolBox* boxes,
                             const uint32_t* tstart, const PoolMeta* meta, int k, int block,
                             int grid, bool one, hipStream_t stream)

@@ -2,6 +2,7 @@
 // storage form and stabilizer mode.  The build compiles this file once per
 // pair (KBC_INST_STORAGE in {0, 1, 2, 3}, KBC_INST_EXACT in {0, 1}); the
 // launchers in kbc_kernels.hip reach the kernels through the tables below.
+#include "kbc_pair.h"
 #include "kbc_step.h"
 
 #if !defined(KBC_INST_STORAGE) || !defined(KBC_INST_EXACT)
@@ -97,6 +98,29 @@ PoolFn pool_kernel(int v, int sw, bool one)
 }
 
 template PoolFn pool_kernel<kS>(int, int, bool);
+
+#if KBC_INST_STORAGE == 0 || KBC_INST_STORAGE == 1
+template <int S>
+PairFn pair_kernel(int v)
+{
+    static_assert(S == kS, "instantiated for one storage form only");
+    switch (v) {
+    case V_D: return k_pair<kS, V_D>;
+    case V_DT: return k_pair<kS, V_DT>;
+    case V_DQ: return k_pair<kS, V_DQ>;
+#if KBC_INST_STORAGE == 0
+    // pair_plan takes no FP32 box with a central variant
+    case V_CD: return k_pair<kS, V_CD>;
+    case V_CDT: return k_pair<kS, V_CDT>;
+    case V_CDQ: return k_pair<kS, V_CDQ>;
+    case V_CDTQ: return k_pair<kS, V_CDTQ>;
+#endif
+    default: return k_pair<kS, V_DTQ>;
+    }
+}
+
+template PairFn pair_kernel<kS>(int);
+#endif
 #endif
 
 }  // namespace kbc
