@@ -345,6 +345,34 @@ __host__ __device__ __forceinline__ double log1p_(double x)
     return log1p_series_ok(x) ? log1p_series(x) : log1p(x);
 }
 
+// The same construction for wider intervals: degree 12 on |x| <= 1/8 (dropped
+// coefficients 3.6e-17) and 16 on |x| <= 1/4 (7.4e-17).
+struct Log1p8 {
+    static constexpr int N = 12;
+    static constexpr double c[13] = {
+        0x1.0000000000000p+0,  -0x1.fffffffffffc2p-2, 0x1.5555555555479p-2, -0x1.000000001b3b5p-2,
+        0x1.9999999a07711p-3,  -0x1.555554e89b815p-3, 0x1.2492488022531p-3, -0x1.00005cefa6982p-3,
+        0x1.c71d5bfe7ca28p-4,  -0x1.994c825ce0e00p-4, 0x1.7407a240e474ap-4, -0x1.649c2bd59f6b5p-4,
+        0x1.4a764ef7b2eacp-4};
+};
+struct Log1p4 {
+    static constexpr int N = 16;
+    static constexpr double c[17] = {
+        0x1.0000000000000p+0,  -0x1.fffffffffffb2p-2, 0x1.55555555553efp-2, -0x1.000000000e9acp-2,
+        0x1.99999999e3e09p-3,  -0x1.5555553be7f09p-3, 0x1.249248f52a9c2p-3, -0x1.000009ebed6abp-3,
+        0x1.c71c9008ed58ep-4,  -0x1.99958149c94b6p-4, 0x1.7457ae9fe4a30p-4, -0x1.55cf7b464d207p-4,
+        0x1.3ba45fb129f0fp-4,  -0x1.1c8a893106cdap-4, 0x1.0857a595287c7p-4, -0x1.4609a04a02f6bp-4,
+        0x1.37c7cd22c3b77p-4};
+};
+template <typename C>
+__host__ __device__ __forceinline__ double log1p_poly(double x)
+{
+    double p = C::c[C::N];
+#pragma unroll
+    for (int k = C::N - 1; k >= 0; --k) p = fma(p, x, C::c[k]);
+    return x * p;
+}
+
 // 1/x from the hardware estimate refined by Newton steps (x is a positive
 // normal number here), in place of an IEEE division: two steps take the
 // estimate (relative error near 2^-23) to about one ulp, one step to about
@@ -362,12 +390,73 @@ __host__ __device__ __forceinline__ double rcp_refined_(double x)
 #endif
 }
 
+// ln(1 + x) for any x > -1, to about 2e-16 absolute (the rounding of 1 + x
+// included; the stabilizer's sums need no relative accuracy near zero, where
+// the polynomials above serve): 1 + x = 2^k m with m in [1/sqrt 2, sqrt 2),
+// ln m = 2 atanh t, t = (m - 1)/(m + 1), and atanh t = t + t^3 P(t^2) with P the
+// degree-6 Chebyshev economization of its Taylor series on t^2 <= 0.02944
+// (dropped coefficients 1.6e-16, scaled by 2 t^3 <= 0.011).
+__host__ __device__ __forceinline__ double log1p_any(double x)
+{
+    constexpr double c[7] = {0x1.5555555555558p-2, 0x1.9999999995219p-3, 0x1.2492492e0644ep-3,
+                             0x1.c71c62cbfea3fp-4, 0x1.7462bba41c635p-4, 0x1.39fd807189bb6p-4,
+                             0x1.2b62ca3da2e33p-4};
+    const double v = 1.0 + x;
+#if defined(__HIP_DEVICE_COMPILE__)
+    double m = __builtin_amdgcn_frexp_mant(v);
+    int k = __builtin_amdgcn_frexp_exp(v);
+#else
+    int k;
+    double m = __builtin_frexp(v, &k);
+#endif
+    const bool low = m < 0x1.6a09e667f3bcdp-1;
+    m = low ? m + m : m;
+    k = low ? k - 1 : k;
+    const double t = (m - 1.0) * rcp_refined_(m + 1.0);
+    const double u = t * t;
+    double p = c[6];
+#pragma unroll
+    for (int j = 5; j >= 0; --j) p = fma(p, u, c[j]);
+    const double t2 = t + t;
+    return fma((double)k, 0x1.62e42fefa39efp-1, fma(t2 * u, p, t2));
+}
+
+// Whether a condition holds at any node of the wavefront (on the host: at
+// this node), so that the branch it selects is one for the whole wave.
+__host__ __device__ __forceinline__ bool any_in_wave(bool c)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ballot_w64(c) != 0;
+#else
+    return c;
+#endif
+}
+
+// Hides a value's origin from the compiler (device code), so that what is
+// formed from it is formed again rather than kept in registers.
+template <typename R>
+__host__ __device__ __forceinline__ void hide(R& v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(v));
+#endif
+}
+
+// No instruction is scheduled across (device code): bounds how many
+// populations' intermediates are in registers at once.
+__host__ __device__ __forceinline__ void end_group()
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
 // Exact stabilizer (section IV, Eq. result1): the root in gamma of
 //   G(gamma) = sum_i dh_i ln(1 + x_i),  x_i = ((1 - beta gamma) dh_i - (2 beta - 1) ds_i) / f^eq_i,
-// where 1 + x_i = f'_i / f^eq_i.  The caller passes, per population, dh_i,
-// hw_i = dh_i / f^eq_i and cc_i = (dh_i - (2 beta - 1) ds_i) / f^eq_i, so that
-// x_i = cc_i - beta gamma hw_i.  With r_i = hw_i / (1 + x_i) and
-// M_k = sum_i dh_i r_i^k,
+// where 1 + x_i = f'_i / f^eq_i.  The caller passes dh_i,
+// ee_i = dh_i - (2 beta - 1) ds_i (ee_of(i)) and 1 / f^eq_i (w_of(i)), so that
+// x_i = (ee_i - beta gamma dh_i) / f^eq_i; refresh() has them formed or read
+// again.  With hw_i = dh_i / f^eq_i, r_i = hw_i / (1 + x_i) and M_k = sum_i dh_i r_i^k,
 //   G'  = -beta   M_1,   G'' = -beta^2 M_2,
 // and, exactly, G(gamma + d) = G(gamma) - sum_{k>=1} (beta d)^k M_k / k.
 // On the interval where all 1 + x_i are positive G falls strictly (M_1 > 0),
@@ -386,17 +475,18 @@ __host__ __device__ __forceinline__ double rcp_refined_(double x)
 // to begin with.  Two Halley steps in a row bound the next one (at least
 // quadratic convergence: s_{n+1} <~ s_n^3 / s_{n-1}^2), and when that bound
 // is already below the tolerance the search stops without evaluating G
-// again.  From gamma* (first-order accurate) one pass suffices at almost
-// every node.  Returns false, leaving gamma to the caller, when no bracket
-// exists.
-__host__ __device__ inline bool gamma_exact_root(const double (&dh)[27], const double (&hw)[27],
-                                                 const double (&cc)[27], double beta, double g0,
-                                                 double& gamma)
+// again.  Returns false, leaving gamma to the caller, when no bracket exists.
+// This is the general search, which gamma_exact_fast leaves few nodes to.
+template <typename EFn, typename WFn, typename RefreshFn>
+__host__ __device__ __forceinline__ bool gamma_exact_root(const double (&dh)[27], EFn ee_of,
+                                                          WFn w_of, RefreshFn refresh,
+                                                          double beta, double g0, double& gamma)
 {
     const double inf = __builtin_inf();
     double lo = -inf, hi = inf, hmax = 0.0;
 #pragma unroll
     for (int i = 0; i < 27; ++i) {
+        const double hw = dh[i] * w_of(i);
         // 1 + x_i > 0  <=>  beta gamma hw_i < 1 + cc_i (hw_i has the sign of
         // dh_i; where it is 0 the population gives no bound); no branches, so
         // that the 27 terms stay one block of code
@@ -404,43 +494,38 @@ __host__ __device__ inline bool gamma_exact_root(const double (&dh)[27], const d
         // near 2^-44) moved inward by 2^-40 of itself, so it never lies
         // outside the exact one; the root is far inside (G runs to -inf /
         // +inf at the ends).
-        hmax = fmax(hmax, fabs(hw[i]));
-        const double ah = fabs(beta * hw[i]);
-        const double b = (1.0 + cc[i]) * rcp_refined_<1>(ah);   // bound on +-gamma
+        hmax = fmax(hmax, fabs(hw));
+        const double ah = fabs(beta * hw);
+        const double b = (1.0 + ee_of(i) * w_of(i)) * rcp_refined_<1>(ah);   // bound on +-gamma
         const double shrink = fabs(b) * 0x1p-40;
-        hi = hw[i] > 0.0 ? fmin(hi, b - shrink) : hi;
-        lo = hw[i] < 0.0 ? fmax(lo, -b + shrink) : lo;
+        hi = hw > 0.0 ? fmin(hi, b - shrink) : hi;
+        lo = hw < 0.0 ? fmax(lo, -b + shrink) : lo;
+        if (i % 3 == 2) end_group();
     }
     if (!(lo < hi) || !(lo > -inf) || !(hi < inf)) return false;
     double g = (g0 > lo && g0 < hi) ? g0 : 0.5 * (lo + hi);
     const double dg_tol = 1e-16 / (beta * hmax);
     double prev = 0.0;   // size of the last step (0: none yet)
     for (int it = 0; it < 80; ++it) {
-        // G by the series wherever it holds (no branch per population: one
-        // block of straight code); a node with some |x_i| >= 1/16 sums G
-        // again with the library logarithm.  With r_i = hw_i / (1 + x_i) the
-        // same pass forms M_k = sum_i dh_i r_i^k, k = 1..4 (each term of M_1
-        // is dh_i^2 / (f^eq_i (1 + x_i)) >= 0, so |M_k| <= rmax^(k-1) M_1).
+        // G and, with r_i = hw_i / (1 + x_i), M_k = sum_i dh_i r_i^k, k = 1..4 (each
+        // term of M_1 is dh_i^2 / (f^eq_i (1 + x_i)) >= 0, so
+        // |M_k| <= rmax^(k-1) M_1)
         double G = 0.0, M1 = 0.0, M2 = 0.0, M3 = 0.0, M4 = 0.0, rmax = 0.0;
-        bool series = true;
         const double bg = beta * g;
+        refresh();
 #pragma unroll
         for (int i = 0; i < 27; ++i) {
-            const double x = cc[i] - bg * hw[i];
-            series = series && log1p_series_ok(x);
-            G += dh[i] * log1p_series(x);
-            const double r = hw[i] * rcp_refined_(1.0 + x);
+            const double w = w_of(i);
+            const double x = (ee_of(i) - bg * dh[i]) * w;
+            G += dh[i] * log1p_any(x);
+            const double r = dh[i] * w * rcp_refined_(1.0 + x);
             const double t1 = dh[i] * r, t2 = t1 * r, t3 = t2 * r;
             M1 += t1;
             M2 += t2;
             M3 += t3;
             M4 += t3 * r;
             rmax = fmax(rmax, fabs(r));
-        }
-        if (!series) {
-            G = 0.0;
-#pragma unroll
-            for (int i = 0; i < 27; ++i) G += dh[i] * log1p_(cc[i] - bg * hw[i]);
+            if (i % 3 == 2) end_group();
         }
         if (G == 0.0) break;
         if (G > 0.0) lo = g;
@@ -490,12 +575,110 @@ __host__ __device__ inline bool gamma_exact_root(const double (&dh)[27], const d
     return true;
 }
 
+// The root of Eq. result1 as gamma_exact_root finds it, without its bracket and
+// with two more terms of the expansion, from a start given in gamma.  A pass over the
+// populations at g with all |x_i| < 1 gives G and M_1..M_6 and with them the
+// step d; with q = |beta d| max r_i < 1/4 every 1 + x_i stays positive, so
+// g + d lies in the interval on which the root is unique, and the terms
+// dropped after k = 6 move it by at most |d| q^6 / (7 (1 - q)).  Where that is
+// below the tolerance the search ends, otherwise the pass is repeated from
+// g + d.  The wave takes the cheapest logarithm that covers its nodes.
+// Returns false where a condition fails or four passes do not suffice; the
+// caller then takes the general search.
+//
+// The search is arithmetic, FP64 instructions above all.  In developed
+// turbulence on 128^3 nodes (u_rms 0.04, nu = 5e-4, 600 steps: some |x_i| >= 1/4
+// in nearly every wave) the general search from gamma* took the library
+// logarithm and a second pass in nearly every wave; the third-order start
+// leaves a second pass to about 5% of them.  ms per step, the general search
+// alone and with this one before it: 0.743 -> 0.237 there (FP32-X 0.745 ->
+// 0.216), 0.408 -> 0.267 in the first steps of the same box, 0.318 -> 0.254 at
+// u_rms 0.004, 256^3 2.18 -> 1.87 (FP32-X 2.07 -> 1.58), 32^3 0.036 -> 0.018.
+// Two FP64 arrays instead of three (1/f^eq_i is a product of two of twelve
+// values), one of them in LDS, let two waves share a SIMD.
+template <typename EFn, typename WFn, typename RefreshFn>
+__host__ __device__ __forceinline__ bool gamma_exact_fast(const double (&dh)[27], EFn ee_of,
+                                                          WFn w_of, RefreshFn refresh,
+                                                          double beta, double& gamma)
+{
+    bool done = false, bad = false;
+    double g = gamma;
+#pragma unroll 1
+    for (int pass = 0; pass < 4; ++pass) {
+        double bg = beta * g;
+        double xmax = 0.0, hmax = 0.0, rmax = 0.0;
+        double M1 = 0.0, M2 = 0.0, M3 = 0.0, M4 = 0.0, M5 = 0.0, M6 = 0.0;
+        refresh();
+#pragma unroll
+        for (int i = 0; i < 27; ++i) {
+            const double w = w_of(i);
+            const double hw = dh[i] * w;
+            const double x = (ee_of(i) - bg * dh[i]) * w;
+            xmax = fmax(xmax, fabs(x));
+            hmax = fmax(hmax, fabs(hw));
+            const double r = hw * rcp_refined_<1>(1.0 + x);
+            const double t1 = dh[i] * r, t2 = t1 * r, t3 = t2 * r, t4 = t3 * r, t5 = t4 * r;
+            M1 += t1;
+            M2 += t2;
+            M3 += t3;
+            M4 += t4;
+            M5 += t5;
+            M6 += t5 * r;
+            rmax = fmax(rmax, fabs(r));
+        }
+        // The moments end here (the compiler would sink them past the branches
+        // below, with 27 x_i and 27 1/f^eq_i live across), and x_i and 1/f^eq_i
+        // are formed again for the logarithms.
+        for (double* v : {&M1, &M2, &M3, &M4, &M5, &M6, &rmax, &hmax}) hide(*v);
+        hide(bg);
+        refresh();
+        auto sum_log = [&](auto ln) {
+            double G = 0.0;
+#pragma unroll
+            for (int i = 0; i < 27; ++i) {
+                G += dh[i] * ln((ee_of(i) - bg * dh[i]) * w_of(i));
+                if (i % 3 == 2) end_group();
+            }
+            return G;
+        };
+        double G;
+        if (!any_in_wave(!(xmax < 0.0625))) G = sum_log([](double x) { return log1p_series(x); });
+        else if (!any_in_wave(!(xmax < 0.125))) G = sum_log([](double x) { return log1p_poly<Log1p8>(x); });
+        else if (!any_in_wave(!(xmax < 0.25))) G = sum_log([](double x) { return log1p_poly<Log1p4>(x); });
+        else G = sum_log([](double x) { return log1p_any(x); });
+        // Halley's step, then Newton on the expansion: d to about q^8 of itself
+        const double GD2 = G * M2, D1s = M1 * M1;
+        double d = 2.0 * G * M1 * rcp_refined_(beta * (2.0 * D1s + GD2)), last = 0.0;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const double y = beta * d;
+            const double P = G - y * (M1 + y * (0.5 * M2 + y * ((1.0 / 3.0) * M3 + y * (0.25 * M4 +
+                             y * (0.2 * M5 + (1.0 / 6.0) * y * M6)))));
+            const double dP = beta * (M1 + y * (M2 + y * (M3 + y * (M4 + y * (M5 + y * M6)))));
+            last = P * rcp_refined_(dP);
+            d += last;
+        }
+        const double q = fabs(beta * d) * rmax, q2 = q * q;
+        if (!done && !bad) {
+            bad = !(xmax < 1.0 && q < 0.25 && fabs(GD2) <= D1s);
+            // and Newton's method has converged (quadratically: what is left
+            // is of the order of the square of its last correction)
+            done = !bad && fabs(d) * q2 * q2 * q2 * (beta * hmax) <= 6e-16 * (1.0 - q) &&
+                   fabs(beta * last) * rmax <= 1e-8;
+            if (!bad) g += d;
+        }
+        if (!any_in_wave(!done && !bad)) break;
+    }
+    gamma = g;
+    return done;
+}
+
 // dh, gamma and the relaxation, given ds_i (ds_of(i)), f - f^eq (fneq_of(i))
 // and the separable 1/f^eq = iCx[vx+1] * iA9[(vy+1) + 3(vz+1)].  GX selects
 // the exact stabilizer (root of Eq. result1) in place of the estimate gamma*;
 // it then also needs the equilibrium in the stored form (eq_of(i): f^eq_i,
 // or f^eq_i - W_i for the deviation forms, DEV) and in FP64 product form.
-template <typename R, bool GX, bool DEV = false, typename DsFn, typename FneqFn,
+template <typename R, bool GX, bool DEV = false, int BLK = 64, typename DsFn, typename FneqFn,
           typename EqFn = int>
 __host__ __device__ __forceinline__ void kbc_gamma_relax(R (&f)[27], DsFn ds_of, FneqFn fneq_of,
                                                          const R (&iCx)[3], const R (&iA9)[9],
@@ -503,27 +686,59 @@ __host__ __device__ __forceinline__ void kbc_gamma_relax(R (&f)[27], DsFn ds_of,
                                                          EqFn eq_of = 0)
 {
     if constexpr (GX) {
-        // The exact root iterates on three FP64 values per population, formed
-        // once here; f itself is not needed again: with x_i = cc_i -
-        // beta gamma hw_i the post-collision population is
+        // The root search works on two FP64 values per population, formed
+        // once here; f itself is not needed again: with x_i = (ee_i -
+        // beta gamma dh_i) / f^eq_i the post-collision population is
         // f'_i = f^eq_i (1 + x_i) = f_i - beta (2 ds_i + gamma dh_i), so it is
         // rebuilt from the equilibrium, which keeps the live state small.
-        double dh[27], hw[27], cc[27];
-        R sh = R(0), hh = R(0);
+        double dh[27];
+#if defined(__HIP_DEVICE_COMPILE__)
+        __shared__ double ee_lds[27][BLK];
+        auto ee_of = [&](int i) -> double& { return ee_lds[i][threadIdx.x]; };
+#else
+        double ee[27];
+        auto ee_of = [&](int i) -> double& { return ee[i]; };
+#endif
+        // sums for the start: sh, hh as for the estimate, and Bk, Ck below
+        R sh = R(0), hh = R(0), B0 = R(0), B1 = R(0), B2 = R(0);
+        R C0 = R(0), C1 = R(0), C2 = R(0), C3 = R(0);
         const double a = 2.0 * c.beta - 1.0;
+        R cx[3] = {iCx[0], iCx[1], iCx[2]};
+        auto w_of = [&](int i) -> double { return (double)(cx[i % 3] * iA9[i / 3]); };
+        auto refresh = [&] {
+            hide(cx[0]);
+            hide(cx[1]);
+            hide(cx[2]);
+#if defined(__HIP_DEVICE_COMPILE__)
+            asm volatile("" ::: "memory");   // ee is read back, not kept
+#endif
+        };
 #pragma unroll
         for (int i = 0; i < 27; ++i) {
             const R ds = ds_of(i);
             const R fneq = fneq_of(i);
             const R w = iCx[i % 3] * iA9[i / 3];
-            const R wr = (fneq - ds) * w;
+            const R dhr = fneq - ds;
+            const R wr = dhr * w;
             sh += ds * wr;
-            hh += (fneq - ds) * wr;
-            const double dsd = (double)ds, wd = (double)w;
+            hh += dhr * wr;
+            // x_i = cc - beta gamma wr
+            const R cc = (dhr - R(a) * ds) * w;
+            const R pc = dhr * cc * cc, ph = dhr * cc * wr, uh = dhr * wr * wr;
+            B0 += pc;
+            B1 += ph;
+            B2 += uh;
+            C0 += pc * cc;
+            C1 += pc * wr;
+            C2 += ph * wr;
+            C3 += uh * wr;
+            const double dsd = (double)ds;
             dh[i] = (double)fneq - dsd;
-            hw[i] = dh[i] * wd;
-            cc[i] = (dh[i] - a * dsd) * wd;
+            ee_of(i) = dh[i] - a * dsd;
         }
+        // the sums end here (see gamma_exact_fast)
+        for (R* v : {&B0, &B1, &B2, &C0, &C1, &C2, &C3}) hide(*v);
+        refresh();
         double gamma;
         if (c.gamma_fixed) {
             gamma = c.gamma_value;
@@ -531,17 +746,29 @@ __host__ __device__ __forceinline__ void kbc_gamma_relax(R (&f)[27], DsFn ds_of,
             gamma = 2.0;
         } else {
             const double g0 = c.inv_beta - c.c2 * (double)sh / (double)hh;
-            double ge;
-            gamma = gamma_exact_root(dh, hw, cc, c.beta, g0, ge) ? ge : 2.0;
+            // One Newton step from gamma*, where sum dh x = 0, on
+            // sum dh (x - x^2/2 + x^3/3) = 0: the start is of third order in x
+            // (b = beta gamma).
+            const double b = c.beta * g0;
+            const double P = -0.5 * (B0 - b * (2.0 * B1 - b * B2)) +
+                             (1.0 / 3.0) * (C0 - b * (3.0 * C1 - b * (3.0 * C2 - b * C3)));
+            const double dP = (B1 - b * B2) - hh - (C1 - b * (2.0 * C2 - b * C3));
+            const double db = -P * rcp_refined_(dP);
+            gamma = fabs(db) < 0.25 ? g0 + db * c.inv_beta : g0;
+            if (!gamma_exact_fast(dh, ee_of, w_of, refresh, c.beta, gamma)) {
+                double ge;
+                gamma = gamma_exact_root(dh, ee_of, w_of, refresh, c.beta, g0, ge) ? ge : 2.0;
+            }
         }
         if (gout) *gout = gamma;
         const double bg = c.beta * gamma;
+        refresh();
 #pragma unroll
         for (int i = 0; i < 27; ++i) {
             const double eq = eq_of(i);
             const double feq = DEV ? eq + weight(i) : eq;
-            f[i] = R(eq + feq * (cc[i] - bg * hw[i]));
-        }
+            f[i] = R(eq + feq * ((ee_of(i) - bg * dh[i]) * w_of(i)));
+            }
         return;
     } else {
         // dh and the entropic scalar products of Eq. result21
@@ -581,7 +808,7 @@ __host__ __device__ __forceinline__ void kbc_gamma_relax(R (&f)[27], DsFn ds_of,
 }
 
 // Natural-moment variants: ds_i from table s_parts, then kbc_gamma_relax.
-template <typename R, int V, bool GX, bool DEV, typename FneqFn, typename EqFn>
+template <typename R, int V, bool GX, bool DEV, int BLK, typename FneqFn, typename EqFn>
 __host__ __device__ __forceinline__ void kbc_relax(R (&f)[27], const DMom<R>& d, FneqFn fneq_of,
                                                    const R (&iCx)[3], const R (&iA9)[9],
                                                    double rho, const Coll& c, double* gout,
@@ -620,7 +847,7 @@ __host__ __device__ __forceinline__ void kbc_relax(R (&f)[27], const DMom<R>& d,
         }
         return R(sx * sy * sz) * qC;
     };
-    kbc_gamma_relax<R, GX, DEV>(f, ds_of, fneq_of, iCx, iA9, rho, c, gout, eq_of);
+    kbc_gamma_relax<R, GX, DEV, BLK>(f, ds_of, fneq_of, iCx, iA9, rho, c, gout, eq_of);
 }
 
 // Central-moment variants (section IV; appendix), then kbc_gamma_relax.  The
@@ -636,7 +863,7 @@ __host__ __device__ __forceinline__ void kbc_relax(R (&f)[27], const DMom<R>& d,
 //   f_{+1} = (u^2 + u)/2 m0 + (u + 1/2) m1 + m2/2,
 // so ds~ is three separable passes over a 3x3x3 array that holds only the
 // 13 second- and third-order entries kept in s.
-template <typename R, int V, bool GX, bool DEV, typename FneqFn, typename EqFn>
+template <typename R, int V, bool GX, bool DEV, int BLK, typename FneqFn, typename EqFn>
 __host__ __device__ __forceinline__ void kbc_relax_central(R (&f)[27], const DMom<R>& d,
                                                            const R (&u)[3], FneqFn fneq_of,
                                                            const R (&iCx)[3], const R (&iA9)[9],
@@ -715,12 +942,13 @@ __host__ __device__ __forceinline__ void kbc_relax_central(R (&f)[27], const DMo
                 ds[vx + 3 * vy + 9 * vz] = G[0][vx][0] * Z2[0][vy][vz] +
                                            G[0][vx][1] * Z2[1][vy][vz] +
                                            G[0][vx][2] * Z2[2][vy][vz];
-    kbc_gamma_relax<R, GX, DEV>(f, [&](int i) -> R { return ds[i]; }, fneq_of, iCx, iA9, rho, c,
+    kbc_gamma_relax<R, GX, DEV, BLK>(f, [&](int i) -> R { return ds[i]; }, fneq_of, iCx, iA9, rho, c,
                                 gout, eq_of);
 }
 
-// gout, when given, receives the gamma used at this node.
-template <int S, int V, bool GX = false>
+// gout, when given, receives the gamma used at this node.  BLK: with the exact
+// stabilizer, the most threads a workgroup has.
+template <int S, int V, bool GX = false, int BLK = 64>
 __host__ __device__ __forceinline__ void collide(typename Traits<S>::R (&f)[27], const Coll& c,
                                                  double* gout = nullptr)
 {
@@ -809,9 +1037,9 @@ __host__ __device__ __forceinline__ void collide(typename Traits<S>::R (&f)[27],
         };
         if constexpr (is_central(V)) {
             const R uf[3] = {(R)u[0], (R)u[1], (R)u[2]};
-            kbc_relax_central<R, V, GX, true>(f, d, uf, fneq_of, iCx, iA9, rho, c, gout, eq_of);
+            kbc_relax_central<R, V, GX, true, BLK>(f, d, uf, fneq_of, iCx, iA9, rho, c, gout, eq_of);
         } else {
-            kbc_relax<R, V, GX, true>(f, d, fneq_of, iCx, iA9, rho, c, gout, eq_of);
+            kbc_relax<R, V, GX, true, BLK>(f, d, fneq_of, iCx, iA9, rho, c, gout, eq_of);
         }
     } else {
         // raw moments R_pqr = sum_i f_i vx^p vy^q vz^r (p,q,r <= 2)
@@ -883,17 +1111,30 @@ __host__ __device__ __forceinline__ void collide(typename Traits<S>::R (&f)[27],
             if constexpr (DEV) return f[i] - (A9[yz] * Cx[ax] + R(w1(ax - 1)) * B9[yz]);
             else return f[i] - A9[yz] * Cx[ax];
         };
-        // the equilibrium in the stored form (f^eq, or f^eq - W)
+        // the equilibrium in the stored form (f^eq, or f^eq - W); in FP64 the
+        // exact stabilizer keeps its twelve factors in LDS during the search
+#if defined(__HIP_DEVICE_COMPILE__)
+        __shared__ R eq_lds[GX && !DEV ? 12 : 1][BLK];
+        if constexpr (GX && !DEV) {
+#pragma unroll
+            for (int yz = 0; yz < 9; ++yz) eq_lds[yz][threadIdx.x] = A9[yz];
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) eq_lds[9 + ax][threadIdx.x] = Cx[ax];
+        }
+#endif
         auto eq_of = [&](int i) -> double {
             const int ax = i % 3, yz = i / 3;
+#if defined(__HIP_DEVICE_COMPILE__)
+            if constexpr (GX && !DEV) return eq_lds[yz][threadIdx.x] * eq_lds[9 + ax][threadIdx.x];
+#endif
             if constexpr (DEV) return (double)(A9[yz] * Cx[ax] + R(w1(ax - 1)) * B9[yz]);
             else return (double)(A9[yz] * Cx[ax]);
         };
         if constexpr (is_central(V))
-            kbc_relax_central<R, V, GX, DEV>(f, d, u, fneq_of, iCx, iA9, (double)rho, c, gout,
+            kbc_relax_central<R, V, GX, DEV, BLK>(f, d, u, fneq_of, iCx, iA9, (double)rho, c, gout,
                                              eq_of);
         else
-            kbc_relax<R, V, GX, DEV>(f, d, fneq_of, iCx, iA9, (double)rho, c, gout, eq_of);
+            kbc_relax<R, V, GX, DEV, BLK>(f, d, fneq_of, iCx, iA9, (double)rho, c, gout, eq_of);
     }
 }
 

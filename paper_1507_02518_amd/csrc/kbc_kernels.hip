@@ -565,10 +565,8 @@ hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gam
     case ST_F32X: *fn = exact_gamma ? step_kernel<ST_F32X, true>(variant, sweep, c64) : step_kernel<ST_F32X, false>(variant, sweep, c64); break;
     default: *fn = exact_gamma ? step_kernel<ST_F16, true>(variant, sweep, c64) : step_kernel<ST_F16, false>(variant, sweep, c64); break;
     }
-    // One wavefront per workgroup for the exact stabilizer (one wave per
-    // SIMD: 64-thread workgroups fill the CUs more evenly; at 256^3 the pull
-    // sweep ran 14% (FP64) and 5% (FP32-X) faster than with 256 threads, the
-    // AA sweeps 12% and 8%), kStepBlock threads otherwise (64 measured within
+    // One wavefront per workgroup for the exact stabilizer (two waves per
+    // SIMD, and LDS for 64 threads: `collide`), kStepBlock threads otherwise (64 measured within
     // +-2% for the other pull forms, 5% slower for FP16 pull, and 17-33%
     // slower for the AA sweeps).
     *block = exact_gamma ? 64u : (uint32_t)kStepBlock;

@@ -294,17 +294,17 @@ __device__ __forceinline__ uint32_t step_block(uint32_t b, uint32_t grid, uint32
 }
 
 // Fused step of one box: one thread per node, workgroups of up to
-// kStepBlock threads (the launch picks the size).  GX: exact stabilizer.
+// kStepBlock threads (the launch picks the size).  GX: exact stabilizer,
+// which fits two waves per SIMD with one of its FP64 arrays in LDS (13.5 KB
+// per wave, 19.5 KB in FP64 with the equilibrium's factors; with the arrays in
+// registers it spilled at two waves and ran 1.6x slower at 256^3 in FP64).
 // C64: pull sweep on 64-node chunks (node_update).
-#ifndef KBC_GX_WAVES_PER_EU
-#define KBC_GX_WAVES_PER_EU 1
-#endif
 template <int S, int V, int SW, bool GX, bool C64 = false>
 __global__ void __launch_bounds__(kStepBlock)
 #if KBC_WAVES_PER_EU
 __attribute__((amdgpu_waves_per_eu(KBC_WAVES_PER_EU, 8)))
 #else
-__attribute__((amdgpu_waves_per_eu(GX ? KBC_GX_WAVES_PER_EU : 1, 8)))
+__attribute__((amdgpu_waves_per_eu(GX ? 2 : 1, 8)))
 #endif
 k_step(StepParams p)
 {
@@ -487,7 +487,7 @@ __global__ void __launch_bounds__(kBlock) k_gamma_stats(int layout, const void* 
             f[i] = decode<S>(static_cast<const T*>(buf)[idx], lc.inv_scale[slot]);
         }
         double gam = 0.0;
-        collide<S, V, GX>(f, c, &gam);
+        collide<S, V, GX, kBlock>(f, c, &gam);
         sum += gam;
         sum2 += gam * gam;
         lo = fmin(lo, gam);
