@@ -119,10 +119,10 @@ void kbc_options_default(kbc_options* opt);
  * first use, kept until kbc_destroy: the velocity field the diagnostics
  * reduce over (24 B per node; 8 B more per node for a density that is read
  * or passed in) for kbc_init_velocity from host memory, kbc_moments,
- * kbc_energy, kbc_energy_series, kbc_enstrophy, kbc_statistics and
- * kbc_correlation; an FP64 copy of the populations (216 B per node) for
- * kbc_get_populations and kbc_set_populations.  kbc_init_velocity_device,
- * kbc_step, kbc_sample_populations, kbc_gamma_statistics and the
+ * kbc_enstrophy, kbc_statistics and kbc_correlation; an FP64 copy of the
+ * populations (216 B per node) for kbc_get_populations and
+ * kbc_set_populations.  kbc_init_velocity_device, kbc_step, kbc_energy,
+ * kbc_energy_series, kbc_sample_populations, kbc_gamma_statistics and the
  * no-allocation energy series add none of them. */
 int kbc_create(const int64_t shape[3], double nu, int32_t dtype,
                const kbc_options* opt, kbc_handle* out);
@@ -174,7 +174,7 @@ int kbc_energy_series(kbc_handle h, int64_t n, double* k);
  * does (the same sums in the same order), but reads the velocity straight
  * from the populations and keeps its partial sums and the log of k in a
  * static device array of the library instead of device buffers:
- * 0 <= n <= KBC_NOALLOC_MAX_STEPS, else KBC_EINVAL.  The array (about 540 KB)
+ * 0 <= n <= KBC_NOALLOC_MAX_STEPS, else KBC_EINVAL.  The array (about 690 KB)
  * exists once per GPU the library runs on and is held until the process
  * ends; its address is looked up on the first call on each device.  Every
  * call on a GPU uses that GPU's array, so calls that overlap on one GPU (from

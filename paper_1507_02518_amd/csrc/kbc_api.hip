@@ -93,8 +93,8 @@ struct kbc_box {
     double* d_u;
     double* d_rho;
     double* d_partial;
-    double* d_sum;      // [0..2] mean sums, [3..5] second reduction, [8..15]
-                        // gradient statistics, [16..19] gamma statistics
+    double* d_sum;      // [0..4] sums of launch_fields, [5] curl, [8..15] gradient
+                        // statistics, [16..19] gamma statistics
     int* d_flag;
     unsigned* d_max;
     double* d_pop;      // canonical staging [27][N]
@@ -135,7 +135,8 @@ void* state_buf(const kbc_box* h)
 // sums, the non-finite flag, the FP16 maxima.
 int ensure_small(kbc_handle h)
 {
-    if (!h->d_partial) KBC_HIP(hipMalloc(&h->d_partial, 8 * (size_t)reduce_partials() * sizeof(double)));
+    const size_t partial = (size_t)std::max(8 * reduce_partials(), energy_partials());
+    if (!h->d_partial) KBC_HIP(hipMalloc(&h->d_partial, partial * sizeof(double)));
     if (!h->d_sum) KBC_HIP(hipMalloc(&h->d_sum, 32 * sizeof(double)));
     if (!h->d_flag) KBC_HIP(hipMalloc(&h->d_flag, sizeof(int)));
     if (!h->d_max) KBC_HIP(hipMalloc(&h->d_max, 27 * sizeof(unsigned)));
@@ -182,19 +183,24 @@ void choose_scales(kbc_handle h, const unsigned* max_bits)
     h->scales_set = true;
 }
 
-// Moments of the current state into h->d_u / h->d_rho; returns KBC_EUNSTABLE
-// when a value is not finite.
-int compute_moments(kbc_handle h, bool want_rho)
+// Enqueues the pass over the current state: the energy sums into d_sum[0..4],
+// and with `fields` the velocity into d_u (and the density into d_rho).
+int enqueue_fields(kbc_handle h, bool fields, bool want_rho)
 {
-    int r = ensure_diag(h, want_rho);
-    if (r) return r;
-    KBC_HIP(hipMemsetAsync(h->d_flag, 0, sizeof(int), h->stream));
-    KBC_HIP(launch_moments(h->dtype, layout_now(h), state_buf(h), h->g, h->inv_scale,
-                           want_rho ? h->d_rho : nullptr, h->d_u, h->d_flag, h->stream));
-    int flag = 0;
-    KBC_HIP(hipMemcpyAsync(&flag, h->d_flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    if (int r = fields ? ensure_diag(h, want_rho) : ensure_small(h)) return r;
+    KBC_HIP(launch_fields(h->dtype, layout_now(h), state_buf(h), h->g, h->inv_scale,
+                          want_rho ? h->d_rho : nullptr, fields ? h->d_u : nullptr, h->d_partial,
+                          h->d_sum, nullptr, h->stream));
+    return KBC_OK;
+}
+
+// The first `n` sums to the host, with the wait for what is enqueued before;
+// KBC_EUNSTABLE when some node was not finite.
+int read_sums(kbc_handle h, double* s, int n)
+{
+    KBC_HIP(hipMemcpyAsync(s, h->d_sum, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     KBC_HIP(hipStreamSynchronize(h->stream));
-    if (flag) return fail(KBC_EUNSTABLE, "state is not finite (the run has diverged)");
+    if (s[4] != 0.0) return fail(KBC_EUNSTABLE, "state is not finite (the run has diverged)");
     return KBC_OK;
 }
 
@@ -316,14 +322,15 @@ int build_graph(kbc_handle h)
 // code object loads there; it stays until the process ends).  Host code
 // reaches it only through the address hipGetSymbolAddress returns for the
 // current device: the array's name in host code is not a device address.
-//   [0, kScrPartial)                 per-block partial sums of a reduction
-//   [kScrPartial, +8)                the sums of u (and spare)
-//   [kScrPartial + 8, + max steps)   k after each step, copied out at the end
+//   [0, kScrPartial)                 the groups' partial sums (launch_fields)
+//   [kScrPartial, +8)                the sums over all nodes (and spare)
+//   [kScrPartial + 8, + max steps)   sum of |u - <u>|^2 after each step, copied
+//                                    out at the end
 // Nothing in it has to start at zero: every value is written before it is
 // read.  Calls on one GPU share the array.
 // ---------------------------------------------------------------------------
 constexpr int64_t kNoAllocMaxSteps = KBC_NOALLOC_MAX_STEPS;
-constexpr size_t kScrPartial = 3 * 1024;
+constexpr size_t kScrPartial = 5 * 4096;
 constexpr size_t kScrSums = 8;
 constexpr size_t kScrDoubles = kScrPartial + kScrSums + (size_t)kNoAllocMaxSteps;
 constexpr int kMaxDevices = 64;
@@ -612,7 +619,9 @@ int kbc_moments(kbc_handle h, double* rho, double* u)
     if (int r = check_handle(h)) return r;
     if (!h->initialised) return fail(KBC_ESTATE, "box has no state");
     if (int r = set_device(h)) return r;
-    const int st = compute_moments(h, rho != nullptr);
+    if (int r = enqueue_fields(h, true, rho != nullptr)) return r;
+    double s[5];
+    const int st = read_sums(h, s, 5);
     if (st != KBC_OK && st != KBC_EUNSTABLE) return st;
     const size_t N = h->g.nnodes;
     if (rho) KBC_HIP(hipMemcpy(rho, h->d_rho, N * sizeof(double), hipMemcpyDeviceToHost));
@@ -621,25 +630,16 @@ int kbc_moments(kbc_handle h, double* rho, double* u)
     return st;
 }
 
-static int mean_sums(kbc_handle h)
-{
-    KBC_HIP(launch_reduce(0, h->g, h->d_u, nullptr, h->d_partial, h->d_sum, h->stream));
-    return KBC_OK;
-}
-
 int kbc_energy(kbc_handle h, double* k)
 {
     if (int r = check_handle(h)) return r;
     if (!k) return fail(KBC_EINVAL, "k is NULL");
     if (!h->initialised) return fail(KBC_ESTATE, "box has no state");
     if (int r = set_device(h)) return r;
-    if (int r = compute_moments(h, false)) return r;
-    if (int r = mean_sums(h)) return r;
-    KBC_HIP(launch_reduce(1, h->g, h->d_u, h->d_sum, h->d_partial, h->d_sum + 3, h->stream));
-    double s = 0.0;
-    KBC_HIP(hipMemcpyAsync(&s, h->d_sum + 3, sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    KBC_HIP(hipStreamSynchronize(h->stream));
-    *k = 0.5 * s / (double)h->g.nnodes;
+    if (int r = enqueue_fields(h, false, false)) return r;
+    double s[5];
+    if (int r = read_sums(h, s, 5)) return r;
+    *k = 0.5 * s[3] / (double)h->g.nnodes;
     return KBC_OK;
 }
 
@@ -651,40 +651,32 @@ int kbc_energy_series(kbc_handle h, int64_t n, double* k)
     if (!h->initialised) return fail(KBC_ESTATE, "box has no state (call kbc_init_velocity)");
     if (n == 0) return KBC_OK;
     if (int r = set_device(h)) return r;
-    if (int r = ensure_diag(h, false)) return r;
-    double* d_log = nullptr;
+    if (int r = ensure_small(h)) return r;
+    double* d_log = nullptr;   // sum of |u - <u>|^2 after each step
     KBC_HIP(hipMalloc(&d_log, (size_t)n * sizeof(double)));
-    // the non-finite flag accumulates over the n moment launches
-    hipError_t e = hipMemsetAsync(h->d_flag, 0, sizeof(int), h->stream);
+    // d_sum[6] counts the nodes that were not finite over the n passes
+    hipError_t e = hipMemsetAsync(h->d_sum + 6, 0, sizeof(double), h->stream);
     int r = e == hipSuccess ? KBC_OK : hip_fail(e, "hipMemsetAsync");
     for (int64_t j = 0; j < n && r == KBC_OK; ++j) {
         r = kbc_step(h, 1);
         if (r != KBC_OK) break;
-        e = launch_moments(h->dtype, layout_now(h), state_buf(h), h->g, h->inv_scale, nullptr,
-                           h->d_u, h->d_flag, h->stream);
-        if (e == hipSuccess)
-            e = launch_reduce(0, h->g, h->d_u, nullptr, h->d_partial, h->d_sum, h->stream);
-        if (e == hipSuccess)
-            e = launch_reduce(1, h->g, h->d_u, h->d_sum, h->d_partial, h->d_sum + 3, h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(d_log + j, h->d_sum + 3, sizeof(double), hipMemcpyDeviceToDevice,
-                               h->stream);
+        e = launch_fields(h->dtype, layout_now(h), state_buf(h), h->g, h->inv_scale, nullptr,
+                          nullptr, h->d_partial, h->d_sum, d_log + j, h->stream);
         if (e != hipSuccess) r = hip_fail(e, "kbc_energy_series");
     }
-    int flag = 0;
+    double bad = 0.0;
     if (r == KBC_OK) {
         e = hipMemcpyAsync(k, d_log, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(&flag, h->d_flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
+            e = hipMemcpyAsync(&bad, h->d_sum + 6, sizeof(double), hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) r = hip_fail(e, "kbc_energy_series");
     }
     (void)hipStreamSynchronize(h->stream);
     (void)hipFree(d_log);
     if (r != KBC_OK) return r;
-    const double inv2n = 0.5 / (double)h->g.nnodes;
-    for (int64_t j = 0; j < n; ++j) k[j] *= inv2n;
-    if (flag) return fail(KBC_EUNSTABLE, "state is not finite (the run has diverged)");
+    for (int64_t j = 0; j < n; ++j) k[j] = 0.5 * k[j] / (double)h->g.nnodes;
+    if (bad != 0.0) return fail(KBC_EUNSTABLE, "state is not finite (the run has diverged)");
     return KBC_OK;
 }
 
@@ -698,7 +690,7 @@ int kbc_energy_series_noalloc(kbc_handle h, int64_t n, double* k)
     if (n > 0 && !k) return fail(KBC_EINVAL, "k is NULL");
     if (!h->initialised) return fail(KBC_ESTATE, "box has no state (call kbc_init_velocity)");
     if (n == 0) return KBC_OK;
-    if (reduce_partials() * 3 > (int)kScrPartial)
+    if (energy_partials() > (int)kScrPartial)
         return fail(KBC_EDEVICE, "reduction partials exceed the scratch array");
     if (int r = set_device(h)) return r;
     double* scr = nullptr;
@@ -708,15 +700,14 @@ int kbc_energy_series_noalloc(kbc_handle h, int64_t n, double* k)
     double* log = scr + kScrPartial + kScrSums;
     for (int64_t j = 0; j < n; ++j) {
         if (int r = step_once(h)) return r;
-        KBC_HIP(launch_energy_direct(h->dtype, layout_now(h), state_buf(h), h->g, h->inv_scale,
-                                     partial, sums, log + j, h->stream));
+        KBC_HIP(launch_fields(h->dtype, layout_now(h), state_buf(h), h->g, h->inv_scale, nullptr,
+                              nullptr, partial, sums, log + j, h->stream));
     }
     KBC_HIP(hipMemcpyAsync(k, log, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     KBC_HIP(hipStreamSynchronize(h->stream));
-    const double inv2n = 0.5 / (double)h->g.nnodes;
     bool finite = true;
     for (int64_t j = 0; j < n; ++j) {
-        k[j] *= inv2n;
+        k[j] = 0.5 * k[j] / (double)h->g.nnodes;
         finite = finite && std::isfinite(k[j]);
     }
     if (!finite) return fail(KBC_EUNSTABLE, "state is not finite (the run has diverged)");
@@ -729,13 +720,11 @@ int kbc_enstrophy(kbc_handle h, double* omega)
     if (!omega) return fail(KBC_EINVAL, "omega is NULL");
     if (!h->initialised) return fail(KBC_ESTATE, "box has no state");
     if (int r = set_device(h)) return r;
-    if (int r = compute_moments(h, false)) return r;
-    if (int r = mean_sums(h)) return r;
-    KBC_HIP(launch_reduce(2, h->g, h->d_u, h->d_sum, h->d_partial, h->d_sum + 3, h->stream));
-    double s = 0.0;
-    KBC_HIP(hipMemcpyAsync(&s, h->d_sum + 3, sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    KBC_HIP(hipStreamSynchronize(h->stream));
-    *omega = 0.5 * s / (double)h->g.nnodes;
+    if (int r = enqueue_fields(h, true, false)) return r;
+    KBC_HIP(launch_curl(h->g, h->d_u, h->d_partial, h->d_sum + 5, h->stream));
+    double s[6];
+    if (int r = read_sums(h, s, 6)) return r;
+    *omega = 0.5 * s[5] / (double)h->g.nnodes;
     return KBC_OK;
 }
 
@@ -746,13 +735,10 @@ int kbc_statistics(kbc_handle h, int32_t order, kbc_stats* out)
     if (order != 2 && order != 8) return fail(KBC_EINVAL, "order must be 2 or 8");
     if (!h->initialised) return fail(KBC_ESTATE, "box has no state");
     if (int r = set_device(h)) return r;
-    if (int r = compute_moments(h, false)) return r;
-    if (int r = mean_sums(h)) return r;
-    KBC_HIP(launch_reduce(1, h->g, h->d_u, h->d_sum, h->d_partial, h->d_sum + 3, h->stream));
+    if (int r = enqueue_fields(h, true, false)) return r;
     KBC_HIP(launch_grad_stats(order, h->g, h->d_u, h->d_partial, h->d_sum + 8, h->stream));
     double s[16];
-    KBC_HIP(hipMemcpyAsync(s, h->d_sum, sizeof(s), hipMemcpyDeviceToHost, h->stream));
-    KBC_HIP(hipStreamSynchronize(h->stream));
+    if (int r = read_sums(h, s, 16)) return r;
     const double N = (double)h->g.nnodes;
     out->k = 0.5 * s[3] / N;
     out->omega = 0.5 * s[8] / N;
@@ -797,21 +783,22 @@ int kbc_correlation(kbc_handle h, int32_t rmax, double* rho11, double* rho22)
     if (rmax < 0 || rmax >= (int)h->g.nx || rmax >= corr_max_lags())
         return fail(KBC_EINVAL, "rmax must be in [0, nx)");
     if (int r = set_device(h)) return r;
-    if (int r = compute_moments(h, false)) return r;
-    if (int r = mean_sums(h)) return r;
+    if (int r = enqueue_fields(h, true, false)) return r;
     const size_t L2 = 2 * (size_t)(rmax + 1);
     double* part = nullptr;
     double* dout = nullptr;
-    KBC_HIP(hipMalloc(&part, (size_t)corr_blocks(h->g) * L2 * sizeof(double)));
+    KBC_HIP(hipMalloc(&part, corr_partials(h->g, rmax) * sizeof(double)));
     hipError_t e = hipMalloc(&dout, L2 * sizeof(double));
     std::vector<double> host(L2);
     if (e == hipSuccess) e = launch_corr_x(h->g, h->d_u, h->d_sum, rmax, part, dout, h->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(host.data(), dout, L2 * sizeof(double), hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    double s[5];
+    const int st = e == hipSuccess ? read_sums(h, s, 5) : KBC_OK;
     (void)hipFree(part);
     if (dout) (void)hipFree(dout);
     if (e != hipSuccess) return fail(KBC_EDEVICE, hipGetErrorString(e));
+    if (st != KBC_OK) return st;
     for (int r = 0; r <= rmax; ++r) {
         rho11[r] = host[2 * r] / host[0];
         rho22[r] = host[2 * r + 1] / host[1];

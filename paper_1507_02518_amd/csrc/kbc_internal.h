@@ -197,19 +197,24 @@ hipError_t launch_sample_pop(int storage, int layout, const void* buf, const Geo
                              const float* inv_scale, const uint32_t* nodes, int count,
                              double* out, hipStream_t stream);
 
-// rho [N] (nullable) and u [3][N] of F(t); sets *flag if a value is not finite.
-hipError_t launch_moments(int storage, int layout, const void* buf, const Geom& g,
-                          const float* inv_scale, double* rho, double* u, int* flag,
-                          hipStream_t stream);
+// One pass over F(t): rho [N] (nullable) and u [3][N] (both NULL: not stored),
+// and out[0..2] = sum_x u_a(x), out[3] = sum_x |u(x) - <u>|^2, out[4] = nodes
+// where a value is not finite; the same bits whether u is stored or not.
+// partial: device scratch of energy_partials() doubles; with
+// log (may be NULL) it receives out[3], and out[4] is added to out[6].
+int energy_partials();
+hipError_t launch_fields(int storage, int layout, const void* buf, const Geom& g,
+                         const float* inv_scale, double* rho, double* u, double* partial,
+                         double* out, double* log, hipStream_t stream);
 
 // Plain streaming copy of n16 16-byte words.
 hipError_t launch_copy16(void* dst, const void* src, size_t n16, hipStream_t stream);
 hipError_t launch_rewrite16(void* p, size_t n16, hipStream_t stream);
 
 // Deterministic FP64 reductions over a velocity field u [3][N].
-//   kind 0: out[0..2] = sum_x u_a(x)
-//   kind 1: out[0]    = sum_x |u(x) - mean|^2     (mean = in[0..2] / N)
-//   kind 2: out[0]    = sum_x |curl_FD2 u(x)|^2
+// *out = sum_x |curl_FD2 u(x)|^2; partial: reduce_partials().
+hipError_t launch_curl(const Geom& g, const double* u, double* partial, double* out,
+                       hipStream_t stream);
 // Flow statistics.  grad: out[8] = sums over nodes of |curl u|^2,
 // sum_ab (d_a u_b + d_b u_a)^2, (div u)^2, (du_x/dx)^n for n = 2..6, with the
 // central stencil of the given order (2 or 8); partial: reduce_partials() * 8.
@@ -223,26 +228,16 @@ hipError_t launch_gamma_stats(int storage, int variant, bool exact_gamma, int la
                               hipStream_t stream);
 // x-correlation sums: out[2r + c] = sum over nodes of u'_c(x) u'_c(x + r),
 // c = 0 (x component), 1 (y component), r = 0..rmax; requires
-// nx <= corr_max_nx(), rmax < corr_max_lags(); partial: corr_blocks(g) *
-// 2 (rmax + 1) doubles; mean_sum: the three sums of u.
+// nx <= corr_max_nx(), rmax < corr_max_lags(); partial: corr_partials(g, rmax)
+// doubles; mean_sum: the three sums of u.
 int corr_max_nx();
 int corr_max_lags();
-int corr_blocks(const Geom& g);
+size_t corr_partials(const Geom& g, int rmax);
 hipError_t launch_corr_x(const Geom& g, const double* u, const double* mean_sum, int rmax,
                          double* partial, double* out, hipStream_t stream);
 
-// Kinetic-energy sum of F(t) read straight from the populations (no velocity
-// field in memory): *out = sum_x |u(x) - mean|^2, the same bits as
-// launch_moments + launch_reduce kinds 0 and 1.  partial: reduce_partials() * 3
-// doubles; sums: 3 doubles (left holding the sums of u).
-hipError_t launch_energy_direct(int storage, int layout, const void* buf, const Geom& g,
-                                const float* inv_scale, double* partial, double* sums,
-                                double* out, hipStream_t stream);
-
-// `partial` is device scratch of reduce_partials() doubles * 3.
+// Blocks of a reduction over u; `partial` holds up to 8 doubles for each.
 int reduce_partials();
-hipError_t launch_reduce(int kind, const Geom& g, const double* u, const double* mean_sum,
-                         double* partial, double* out, hipStream_t stream);
 
 // ---------------------------------------------------------------------------
 // Batched ensemble (pool): many independent AA boxes advanced by one launch.

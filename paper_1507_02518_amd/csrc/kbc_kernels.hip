@@ -6,6 +6,7 @@
 #include <math.h>
 
 #include "kbc_device.h"
+#include "kbc_fields.h"
 #include "kbc_internal.h"
 #include "kbc_step.h"
 
@@ -167,144 +168,173 @@ __global__ void __launch_bounds__(kBlock) k_scatter_pop(int layout, void* buf, G
     }
 }
 
-// rho = sum_i f_i, rho u = sum_i v_i f_i (section I) of node n, in FP64.
-// Deviation forms sum the stored deviations and add the weights' share
-// (1, 0).  Every kernel that needs the velocity of F(t) takes it from here,
-// so they all see the same bits.
-template <int S>
-__device__ __forceinline__ void node_velocity(int layout, const void* buf, const Geom& g,
-                                              const LoadCtx& lc, uint32_t n, double& m,
-                                              double& ux, double& uy, double& uz)
+// Density and velocity of F(t) and the kinetic-energy sums in one pass over the
+// populations (kbc_fields.h on the order): wave w takes the runs w, w + waves,
+// ... and writes its group's sums.  FIELDS: u (and rho where asked for) are
+// stored too.  Bound by reading the populations: FP64 256^3 with u stored
+// 0.87 -> 0.82 ms, FP16 512^3 5.41 -> 2.14 ms against the version with a
+// 64-bit index and a wrap per population.
+template <int S, int LY, bool FIELDS>
+__global__ void __launch_bounds__(kBlock) k_fields(const void* buf, Geom g, LoadCtx lc,
+                                                   double* __restrict__ rho,
+                                                   double* __restrict__ u,
+                                                   EnergySum* __restrict__ groups)
 {
-    uint32_t x, y, z;
-    node_xyz(n, g, x, y, z);
-    double jx = 0.0, jy = 0.0, jz = 0.0;
-    m = 0.0;
-    for (int i = 0; i < 27; ++i) {
-        int slot;
-        const uint64_t idx = locate(layout, i, x, y, z, g, slot);
-        double v = load_full<S>(buf, idx, slot, i, lc.inv_scale);
-        if constexpr (S != ST_F64) v -= weight(i);
-        m += v;
-        jx += vel(i, 0) * v;
-        jy += vel(i, 1) * v;
-        jz += vel(i, 2) * v;
+    using T = typename Traits<S>::T;
+    using R = typename Traits<S>::R;
+    const uint32_t runs = (g.nnodes + 63) / 64, lane = threadIdx.x & 63;
+    const uint32_t wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    const uint32_t waves = runs < kEnergyGroups ? runs : kEnergyGroups;
+    if (wave >= waves) return;
+    EnergyAcc acc;
+    T v[27];
+    auto fetch = [&](uint32_t j) {
+        const uint32_t node = 64 * j + lane;
+        load_node<S, LY>(buf, g, node < g.nnodes ? node : g.nnodes - 1, v);
+    };
+    fetch(wave);
+    for (uint32_t j = wave; j < runs; j += waves) {
+        const uint32_t node = 64 * j + lane;
+        const bool real = node < g.nnodes;
+        R f[27];
+#pragma unroll
+        for (int i = 0; i < 27; ++i) f[i] = decode<S>(v[i], lc.inv_scale[i]);
+        // the next run's populations are on their way while this one is reduced
+        if (j + waves < runs) fetch(j + waves);
+        double m, uu[3];
+        node_velocity<S>(f, m, uu);
+        if constexpr (FIELDS) {
+            if (real) {
+                if (rho) rho[node] = m;
+                u[node] = uu[0];
+                u[g.nnodes + (size_t)node] = uu[1];
+                u[2 * (size_t)g.nnodes + node] = uu[2];
+            }
+        }
+        double inv;
+        const double count = run_count(j, g.nnodes, inv);
+        add_energy(acc, run_energy(real, count, inv, m, uu), count, inv, j == wave);
     }
-    if constexpr (S != ST_F64) m += 1.0;
-    const double ir = 1.0 / m;
-    ux = jx * ir;
-    uy = jy * ir;
-    uz = jz * ir;
+    if (lane == 0) groups[wave] = total_energy(acc);
 }
 
-template <int S>
-__global__ void __launch_bounds__(kBlock) k_moments(int layout, const void* buf, Geom g, LoadCtx lc,
-                                                    double* __restrict__ rho,
-                                                    double* __restrict__ u, int* flag)
+// Nodes of the group w.
+__device__ __forceinline__ double group_count(uint32_t w, uint32_t nnodes)
 {
-    const uint32_t n = blockIdx.x * kBlock + threadIdx.x;
-    if (n >= g.nnodes) return;
-    double m, ux, uy, uz;
-    node_velocity<S>(layout, buf, g, lc, n, m, ux, uy, uz);
-    if (rho) rho[n] = m;
-    u[n] = ux;
-    u[g.nnodes + n] = uy;
-    u[2 * (size_t)g.nnodes + n] = uz;
-    if (!(isfinite(m) && isfinite(ux) && isfinite(uy) && isfinite(uz))) atomicOr(flag, 1);
+    const uint32_t runs = (nnodes + 63) / 64, waves = runs < kEnergyGroups ? runs : kEnergyGroups;
+    const uint32_t mine = (runs - w + waves - 1) / waves;
+    // the last run may be short
+    return 64.0 * mine - ((runs - 1) % waves == w ? 64.0 * runs - (double)nnodes : 0.0);
+}
+
+// The sums over all nodes from the groups': out[0..2] sum of u, [3] sum of
+// |u - <u>|^2, [4] nodes that are not finite.  log (may be NULL) takes out[3] of
+// this step, and out[6] then counts on.  One workgroup; every thread adds its
+// groups to the deviations from the first group's mean, and the five sums
+// are then plain ones.
+constexpr int kFinalBlock = 1024;
+__global__ void __launch_bounds__(kFinalBlock) k_energy_final(const EnergySum* __restrict__ groups,
+                                                              uint32_t nnodes,
+                                                              double* __restrict__ out,
+                                                              double* __restrict__ log)
+{
+#pragma clang fp contract(off)
+    __shared__ double part[kFinalBlock / 64][5];
+    const uint32_t runs = (nnodes + 63) / 64, waves = runs < kEnergyGroups ? runs : kEnergyGroups;
+    const double r0 = 1.0 / group_count(0, nnodes);
+    const double c[3] = {groups[0].s[0] * r0, groups[0].s[1] * r0, groups[0].s[2] * r0};
+    double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};   // sums of n d, of m2 + n d^2, bad
+    for (uint32_t w = threadIdx.x; w < waves; w += kFinalBlock) {
+        const EnergySum e = groups[w];
+        const double n = group_count(w, nnodes), r = 1.0 / n;
+        double d2 = 0.0;
+        for (int k = 0; k < 3; ++k) {
+            const double d = e.s[k] * r - c[k];
+            a[k] += n * d;
+            d2 = k == 0 ? d * d : d2 + d * d;
+        }
+        a[3] += e.m2 + n * d2;
+        a[4] += e.bad;
+    }
+    for (int k = 0; k < 5; ++k) a[k] = wave_sum(a[k]);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0)
+        for (int k = 0; k < 5; ++k) part[wave][k] = a[k];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 0; k < 5; ++k) {
+            a[k] = part[0][k];
+            for (int w = 1; w < kFinalBlock / 64; ++w) a[k] += part[w][k];
+        }
+        const double N = (double)nnodes;
+        for (int k = 0; k < 3; ++k) out[k] = N * c[k] + a[k];
+        const double m2 = a[3] - ((a[0] * a[0] + a[1] * a[1]) + a[2] * a[2]) / N;
+        out[3] = m2;
+        out[4] = a[4];
+        if (log) {
+            *log = m2;
+            out[6] += a[4];
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
 // Deterministic FP64 reductions: fixed grid, fixed per-thread order,
 // butterfly within the wavefront, fixed order across wavefronts and blocks.
 // ---------------------------------------------------------------------------
-constexpr int kReduceBlocks = 1024;
-template <int KIND>
-__global__ void __launch_bounds__(kBlock) k_reduce(Geom g, const double* __restrict__ u,
-                                                   const double* __restrict__ mean_sum,
-                                                   double* __restrict__ partial)
+// Blocks of the reductions over a velocity field: eight per CU, all resident.
+constexpr int kReduceBlocks = 2048;
+
+// Per-block sums of |curl u|^2, second-order central differences on the
+// periodic grid.  A thread marches a column of kCurlPlanes planes and keeps
+// u_x and u_y of three planes; an item is 256 columns of such a run of planes,
+// and the workgroups of one XCD take consecutive items, so that the rows a row
+// is differenced with come from its L2.  Bound by reading u: 512^3 1.17 -> 0.97
+// ms (3.2 GB) against one node per thread in the dispatch order.
+constexpr uint32_t kCurlPlanes = 32;
+
+__global__ void __launch_bounds__(kBlock) k_curl(Geom g, const double* __restrict__ u,
+                                                 double* __restrict__ partial)
 {
     const size_t N = g.nnodes;
-    double acc[3] = {0.0, 0.0, 0.0};
-    double mean[3] = {0.0, 0.0, 0.0};
-    if (KIND != 0)
-        for (int a = 0; a < 3; ++a) mean[a] = mean_sum[a] / (double)N;
-    for (uint32_t n = blockIdx.x * kBlock + threadIdx.x; n < g.nnodes; n += gridDim.x * kBlock) {
-        if (KIND == 0) {
-            for (int a = 0; a < 3; ++a) acc[a] += u[a * N + n];
-        } else if (KIND == 1) {
-            for (int a = 0; a < 3; ++a) {
-                const double d = u[a * N + n] - mean[a];
-                acc[0] += d * d;
-            }
-        } else {
-            uint32_t x, y, z;
-            node_xyz(n, g, x, y, z);
-            const uint32_t xp = node_of(wrap_add(x, 1, g.nx), y, z, g);
-            const uint32_t xm = node_of(wrap_add(x, -1, g.nx), y, z, g);
-            const uint32_t yp = node_of(x, wrap_add(y, 1, g.ny), z, g);
-            const uint32_t ym = node_of(x, wrap_add(y, -1, g.ny), z, g);
-            const uint32_t zp = node_of(x, y, wrap_add(z, 1, g.nz), g);
-            const uint32_t zm = node_of(x, y, wrap_add(z, -1, g.nz), g);
-            auto up = [&](int a, uint32_t m) { return u[a * N + m] - mean[a]; };
-            const double wx = 0.5 * (up(2, yp) - up(2, ym)) - 0.5 * (up(1, zp) - up(1, zm));
-            const double wy = 0.5 * (up(0, zp) - up(0, zm)) - 0.5 * (up(2, xp) - up(2, xm));
-            const double wz = 0.5 * (up(1, xp) - up(1, xm)) - 0.5 * (up(0, yp) - up(0, ym));
-            acc[0] += wx * wx + wy * wy + wz * wz;
-        }
-    }
-    block_sum<3>(acc, partial + 3 * blockIdx.x);
-}
-
-__global__ void __launch_bounds__(kBlock) k_reduce_final(const double* __restrict__ partial,
-                                                         int count, double* __restrict__ out)
-{
-    double acc[3] = {0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < count; b += kBlock)
-        for (int k = 0; k < 3; ++k) acc[k] += partial[3 * b + k];
-    block_sum<3>(acc, out);
-}
-
-// Kinetic energy straight from the populations, without a velocity field in
-// memory: pass 0 sums u over the nodes, pass 1 sums |u - mean|^2 (mean =
-// mean_sum / N).  The grid, the per-thread order and the block reduction are
-// those of k_reduce over a stored field, and u comes from node_velocity as in
-// k_moments, so the sums are the same bits as moments + k_reduce.
-template <int S, int PASS>
-__global__ void __launch_bounds__(kBlock) k_energy_pass(int layout, const void* buf, Geom g,
-                                                        LoadCtx lc,
-                                                        const double* __restrict__ mean_sum,
-                                                        double* __restrict__ partial)
-{
-    const size_t N = g.nnodes;
-    double acc[3] = {0.0, 0.0, 0.0};
-    double mean[3] = {0.0, 0.0, 0.0};
-    if (PASS != 0)
-        for (int a = 0; a < 3; ++a) mean[a] = mean_sum[a] / (double)N;
-    for (uint32_t n = blockIdx.x * kBlock + threadIdx.x; n < g.nnodes; n += gridDim.x * kBlock) {
-        double m, uu[3];
-        node_velocity<S>(layout, buf, g, lc, n, m, uu[0], uu[1], uu[2]);
-        // u as k_moments stores it: rounded, not fused into u - mean below
-        asm volatile("" : "+v"(uu[0]), "+v"(uu[1]), "+v"(uu[2]));
-        if (PASS == 0) {
-            for (int a = 0; a < 3; ++a) acc[a] += uu[a];
-        } else {
-            for (int a = 0; a < 3; ++a) {
-                const double d = uu[a] - mean[a];
-                acc[0] += d * d;
-            }
-        }
-    }
-    block_sum<3>(acc, partial + 3 * blockIdx.x);
-}
-
-// First component of k_reduce_final only (same order, same bits), for a
-// destination with room for one value.
-__global__ void __launch_bounds__(kBlock) k_reduce_final_1(const double* __restrict__ partial,
-                                                           int count, double* __restrict__ out)
-{
+    const double *ux = u, *uy = u + N, *uz = u + 2 * N;
+    const uint32_t slab = g.nx * g.ny;
+    const uint32_t cols = (slab + kBlock - 1) / kBlock;
+    const uint32_t items = cols * ((g.nz + kCurlPlanes - 1) / kCurlPlanes);
+    // eighth of the items of this XCD (workgroup b runs on XCD b mod 8)
+    const uint32_t xcds = gridDim.x < 8 ? 1 : 8;
+    const uint32_t j = blockIdx.x % xcds, q = items / xcds, r = items % xcds;
+    const uint32_t first = j * q + (j < r ? j : r), last = first + q + (j < r ? 1 : 0);
     double acc[1] = {0.0};
-    for (int b = threadIdx.x; b < count; b += kBlock) acc[0] += partial[3 * b];
-    block_sum<1>(acc, out);
+    for (uint32_t it = first + blockIdx.x / xcds; it < last; it += (gridDim.x + xcds - 1 - j) / xcds) {
+        const uint32_t c = (it % cols) * kBlock + threadIdx.x;
+        if (c >= slab) continue;
+        const uint32_t z0 = (it / cols) * kCurlPlanes;
+        const uint32_t planes = g.nz - z0 < kCurlPlanes ? g.nz - z0 : kCurlPlanes;
+        const uint32_t y = fdiv(c, g.dnx), x = c - y * g.nx;
+        const uint32_t xp = x + 1 == g.nx ? c - x : c + 1, xm = x == 0 ? c + g.nx - 1 : c - 1;
+        const uint32_t yp = y + 1 == g.ny ? c - y * g.nx : c + g.nx;
+        const uint32_t ym = y == 0 ? c + (g.ny - 1) * g.nx : c - g.nx;
+        size_t here = (size_t)z0 * slab;
+        const size_t below = (size_t)(z0 == 0 ? g.nz - 1 : z0 - 1) * slab;
+        double ax = ux[below + c], ay = uy[below + c];   // plane z - 1
+        double bx = ux[here + c], by = uy[here + c];     // plane z
+        for (uint32_t k = 0; k < planes; ++k) {
+            const size_t up = z0 + k + 1 == g.nz ? 0 : here + slab;
+            const double cx = ux[up + c], cy = uy[up + c];
+            const double *px = ux + here, *py = uy + here, *pz = uz + here;
+            const double wx = 0.5 * (pz[yp] - pz[ym]) - 0.5 * (cy - ay);
+            const double wy = 0.5 * (cx - ax) - 0.5 * (pz[xp] - pz[xm]);
+            const double wz = 0.5 * (py[xp] - py[xm]) - 0.5 * (px[yp] - px[ym]);
+            acc[0] += wx * wx + wy * wy + wz * wz;
+            ax = bx;
+            ay = by;
+            bx = cx;
+            by = cy;
+            here = up;
+        }
+    }
+    block_sum<1>(acc, partial + blockIdx.x);
 }
 
 template <int K>
@@ -682,17 +712,42 @@ hipError_t launch_scatter_pop(int storage, int layout, void* buf, const Geom& g,
     return hipGetLastError();
 }
 
-hipError_t launch_moments(int storage, int layout, const void* buf, const Geom& g,
-                          const float* inv_scale, double* rho, double* u, int* flag,
-                          hipStream_t stream)
+namespace {
+
+template <bool FIELDS>
+using FieldsFn = void (*)(const void*, Geom, LoadCtx, double*, double*, EnergySum*);
+
+template <int S, bool FIELDS>
+FieldsFn<FIELDS> fields_kernel(int layout)
+{
+    return layout == LY_PULL ? k_fields<S, LY_PULL, FIELDS>
+                             : (layout == LY_AA_EVEN ? k_fields<S, LY_AA_EVEN, FIELDS>
+                                                     : k_fields<S, LY_AA_ODD, FIELDS>);
+}
+
+}  // namespace
+
+static_assert(sizeof(EnergySum) == 5 * sizeof(double), "energy_partials() counts doubles");
+int energy_partials() { return 5 * (int)kEnergyGroups; }
+
+hipError_t launch_fields(int storage, int layout, const void* buf, const Geom& g,
+                         const float* inv_scale, double* rho, double* u, double* partial,
+                         double* out, double* log, hipStream_t stream)
 {
     if (storage == ST_F32X) storage = ST_F32;  // same storage format
+    // the AA layouts are planes (load_node)
+    if (layout != LY_PULL && !geom_is_planes(g)) return hipErrorInvalidValue;
     LoadCtx lc;
     for (int i = 0; i < 27; ++i) lc.inv_scale[i] = inv_scale ? inv_scale[i] : 1.0f;
-    const dim3 grid(grid_for(g.nnodes)), block(kBlock);
-    if (storage == ST_F64) hipLaunchKernelGGL(k_moments<ST_F64>, grid, block, 0, stream, layout, buf, g, lc, rho, u, flag);
-    else if (storage == ST_F32) hipLaunchKernelGGL(k_moments<ST_F32>, grid, block, 0, stream, layout, buf, g, lc, rho, u, flag);
-    else hipLaunchKernelGGL(k_moments<ST_F16>, grid, block, 0, stream, layout, buf, g, lc, rho, u, flag);
+    const uint32_t runs = (uint32_t)(((uint64_t)g.nnodes + 63) / 64);
+    const uint32_t waves = std::min(runs, kEnergyGroups);
+    const dim3 grid((waves + kBlock / 64 - 1) / (kBlock / 64)), block(kBlock);
+    EnergySum* groups = reinterpret_cast<EnergySum*>(partial);
+    const auto fn = storage == ST_F64   ? (u ? fields_kernel<ST_F64, true>(layout) : fields_kernel<ST_F64, false>(layout))
+                    : storage == ST_F32 ? (u ? fields_kernel<ST_F32, true>(layout) : fields_kernel<ST_F32, false>(layout))
+                                        : (u ? fields_kernel<ST_F16, true>(layout) : fields_kernel<ST_F16, false>(layout));
+    hipLaunchKernelGGL(fn, grid, block, 0, stream, buf, g, lc, rho, u, groups);
+    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kFinalBlock), 0, stream, groups, g.nnodes, out, log);
     return hipGetLastError();
 }
 
@@ -718,36 +773,14 @@ hipError_t launch_rewrite16(void* p, size_t n16, hipStream_t stream)
 
 int reduce_partials() { return kReduceBlocks; }
 
-hipError_t launch_reduce(int kind, const Geom& g, const double* u, const double* mean_sum,
-                         double* partial, double* out, hipStream_t stream)
+hipError_t launch_curl(const Geom& g, const double* u, double* partial, double* out,
+                       hipStream_t stream)
 {
-    const unsigned blocks = std::min<unsigned>(kReduceBlocks, grid_for(g.nnodes));
-    if (kind == 0) hipLaunchKernelGGL(k_reduce<0>, dim3(blocks), dim3(kBlock), 0, stream, g, u, mean_sum, partial);
-    else if (kind == 1) hipLaunchKernelGGL(k_reduce<1>, dim3(blocks), dim3(kBlock), 0, stream, g, u, mean_sum, partial);
-    else hipLaunchKernelGGL(k_reduce<2>, dim3(blocks), dim3(kBlock), 0, stream, g, u, mean_sum, partial);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kBlock), 0, stream, partial, (int)blocks, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_energy_direct(int storage, int layout, const void* buf, const Geom& g,
-                                const float* inv_scale, double* partial, double* sums,
-                                double* out, hipStream_t stream)
-{
-    if (storage == ST_F32X) storage = ST_F32;  // same storage format
-    LoadCtx lc;
-    for (int i = 0; i < 27; ++i) lc.inv_scale[i] = inv_scale ? inv_scale[i] : 1.0f;
-    const unsigned blocks = std::min<unsigned>(kReduceBlocks, grid_for(g.nnodes));
-    const dim3 grid(blocks), block(kBlock);
-    if (storage == ST_F64) hipLaunchKernelGGL((k_energy_pass<ST_F64, 0>), grid, block, 0, stream, layout, buf, g, lc, sums, partial);
-    else if (storage == ST_F32) hipLaunchKernelGGL((k_energy_pass<ST_F32, 0>), grid, block, 0, stream, layout, buf, g, lc, sums, partial);
-    else hipLaunchKernelGGL((k_energy_pass<ST_F16, 0>), grid, block, 0, stream, layout, buf, g, lc, sums, partial);
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kBlock), 0, stream, partial, (int)blocks, sums);
-    if (storage == ST_F64) hipLaunchKernelGGL((k_energy_pass<ST_F64, 1>), grid, block, 0, stream, layout, buf, g, lc, sums, partial);
-    else if (storage == ST_F32) hipLaunchKernelGGL((k_energy_pass<ST_F32, 1>), grid, block, 0, stream, layout, buf, g, lc, sums, partial);
-    else hipLaunchKernelGGL((k_energy_pass<ST_F16, 1>), grid, block, 0, stream, layout, buf, g, lc, sums, partial);
-    hipLaunchKernelGGL(k_reduce_final_1, dim3(1), dim3(kBlock), 0, stream, partial, (int)blocks, out);
+    const uint64_t cols = ((uint64_t)g.nx * g.ny + kBlock - 1) / kBlock;
+    const uint64_t items = cols * ((g.nz + kCurlPlanes - 1) / kCurlPlanes);
+    const unsigned blocks = (unsigned)std::min<uint64_t>(kReduceBlocks, items);
+    hipLaunchKernelGGL(k_curl, dim3(blocks), dim3(kBlock), 0, stream, g, u, partial);
+    hipLaunchKernelGGL(k_reduce_final_k<1>, dim3(1), dim3(kBlock), 0, stream, partial, (int)blocks, out);
     return hipGetLastError();
 }
 
@@ -788,12 +821,15 @@ hipError_t launch_gamma_stats(int storage, int variant, bool exact_gamma, int la
 
 int corr_max_nx() { return kCorrMaxN; }
 int corr_max_lags() { return kCorrLags * kBlock; }
-int corr_blocks(const Geom& g) { return (int)std::min<uint32_t>(kReduceBlocks, g.ny * g.nz); }
+size_t corr_partials(const Geom& g, int rmax)
+{
+    return (size_t)std::min<uint32_t>(kReduceBlocks, g.ny * g.nz) * 2 * (rmax + 1);
+}
 
 hipError_t launch_corr_x(const Geom& g, const double* u, const double* mean_sum, int rmax,
                          double* partial, double* out, hipStream_t stream)
 {
-    const int blocks = corr_blocks(g);
+    const int blocks = (int)std::min<uint32_t>(kReduceBlocks, g.ny * g.nz);
     hipLaunchKernelGGL(k_corr_x, dim3(blocks), dim3(kBlock), 0, stream, g, u, mean_sum, rmax, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

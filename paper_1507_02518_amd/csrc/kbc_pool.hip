@@ -451,7 +451,7 @@ int kbc_pool_create(size_t hbm_budget_bytes, int32_t dtype, const kbc_options* o
         e = hipEventCreateWithFlags(&p->mirror_ev[m], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreate(&p->tev0);
     if (e == hipSuccess) e = hipEventCreate(&p->tev1);
-    if (e == hipSuccess) e = hipMalloc(&p->d_partial, 3 * (size_t)reduce_partials() * sizeof(double));
+    if (e == hipSuccess) e = hipMalloc(&p->d_partial, (size_t)std::max(reduce_partials(), energy_partials()) * sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&p->d_sum, 8 * sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&p->d_flag, sizeof(int));
     if (e == hipSuccess) e = hipMalloc(&p->d_max, 27 * sizeof(unsigned));
@@ -772,23 +772,19 @@ int kbc_pool_result(kbc_pool_handle p, int32_t slot, double* k, double* omega, d
     const void* buf = p->arena_base + s.off;
     const int layout = (s.t % 2 == 0) ? LY_AA_EVEN : LY_AA_ODD;
     const int storage = p->dtype == KBC_F32_DEV_X ? KBC_F32_DEV : p->dtype;
-    PHIP(hipMemsetAsync(p->d_flag, 0, sizeof(int), p->diag_stream));
-    PHIP(launch_moments(storage, layout, buf, s.g, s.inv_scale, p->d_rho, p->d_u, p->d_flag,
-                        p->diag_stream));
-    PHIP(launch_reduce(0, s.g, p->d_u, nullptr, p->d_partial, p->d_sum, p->diag_stream));
-    PHIP(launch_reduce(1, s.g, p->d_u, p->d_sum, p->d_partial, p->d_sum + 3, p->diag_stream));
-    PHIP(launch_reduce(2, s.g, p->d_u, p->d_sum, p->d_partial, p->d_sum + 6, p->diag_stream));
-    double sums[8];
-    int flag = 0;
+    // sums[0..4] as launch_fields leaves them, sums[5] of the curl
+    PHIP(launch_fields(storage, layout, buf, s.g, s.inv_scale, rho ? p->d_rho : nullptr, p->d_u,
+                       p->d_partial, p->d_sum, nullptr, p->diag_stream));
+    PHIP(launch_curl(s.g, p->d_u, p->d_partial, p->d_sum + 5, p->diag_stream));
+    double sums[6];
     PHIP(hipMemcpyAsync(sums, p->d_sum, sizeof(sums), hipMemcpyDeviceToHost, p->diag_stream));
-    PHIP(hipMemcpyAsync(&flag, p->d_flag, sizeof(int), hipMemcpyDeviceToHost, p->diag_stream));
     PHIP(hipStreamSynchronize(p->diag_stream));
     const double N = (double)s.g.nnodes;
     if (k) *k = 0.5 * sums[3] / N;
-    if (omega) *omega = 0.5 * sums[6] / N;
+    if (omega) *omega = 0.5 * sums[5] / N;
     if (rho) PHIP(hipMemcpy(rho, p->d_rho, s.g.nnodes * sizeof(double), hipMemcpyDeviceToHost));
     if (u) PHIP(hipMemcpy(u, p->d_u, 3ull * s.g.nnodes * sizeof(double), hipMemcpyDeviceToHost));
-    if (flag) return pfail(KBC_EUNSTABLE, "the box's state is not finite (its run diverged)");
+    if (sums[4] != 0.0) return pfail(KBC_EUNSTABLE, "the box's state is not finite (its run diverged)");
     return KBC_OK;
 }
 

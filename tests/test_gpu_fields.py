@@ -1,0 +1,66 @@
+"""Density, velocity and the sums over nodes at the sizes where their kernels
+can go wrong: fewer nodes than a wavefront, a partial last run, more runs
+than groups, and column marches with remainders."""
+import numpy as np
+import pytest
+
+from paper_1507_02518_amd import inputs, kbc
+from paper_1507_02518_amd.kbc import AA, F16_DEV, F32_DEV, F32_DEV_X, F64, PULL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (5, 3, 2), (70, 9, 33), (33, 16, 65), (64, 64, 66)])
+@pytest.mark.parametrize("dtype,streaming,steps", [
+    (F64, PULL, 3), (F64, AA, 2), (F64, AA, 3), (F32_DEV, PULL, 2), (F32_DEV_X, AA, 3),
+    (F16_DEV, AA, 2), (F16_DEV, PULL, 3)])
+def test_fields_and_sums_match_oracle(orc, shape, dtype, streaming, steps):
+    with kbc.Box(shape, 2e-3, dtype, streaming=streaming) as b:
+        b.init_velocity(inputs.smooth_random(shape, 0.05, seed=3))
+        b.step(steps)
+        f = b.populations()
+        if not np.isfinite(f).all():    # a box this small and rough leaves FP16's range
+            for call in (b.moments, b.energy, b.enstrophy):
+                with pytest.raises(kbc.KbcError) as e:
+                    call()
+                assert e.value.code == kbc.KBC_EUNSTABLE
+            return
+        rho, u = b.moments()
+        k, w2 = b.energy(), b.enstrophy()
+    orho, ou = orc.macros(f)
+    # two sums of 27 terms below 0.3 and, for the deviation forms, one more
+    # rounding of each population: below 27 * 2^-54 each
+    assert np.abs(rho - orho).max() <= 4e-15 and np.abs(u - ou).max() <= 4e-15
+    # sums over nodes of the same u, 64-bit: 1e-12 of the value, and the
+    # rounding of u itself where the flow is uniform
+    assert k == pytest.approx(orc.energy(u), rel=1e-12, abs=1e-30)
+    assert w2 == pytest.approx(orc.enstrophy(u), rel=1e-12, abs=1e-28)
+
+
+@pytest.mark.parametrize("shape", [(5, 3, 2), (70, 9, 33), (64, 64, 66)])
+def test_energy_keeps_its_digits_on_a_mean_flow(shape):
+    """Perturbations of 1e-6 on a uniform flow of 0.1: u is rounded at 1.4e-17
+    and kept to a few of these, 1e-10 of the perturbation."""
+    u0 = inputs.smooth_random(shape, 1e-6, seed=5)
+    u0 += np.array([0.1, -0.07, 0.05])[:, None, None, None]
+    with kbc.Box(shape, 2e-3) as b:
+        b.init_velocity(u0)
+        b.step(1)
+        k, (_, u) = b.energy(), b.moments()
+    d = u.astype(np.longdouble).reshape(3, -1)
+    d = d - d.mean(axis=1, keepdims=True)
+    assert k == pytest.approx(float(0.5 * (d * d).sum(axis=0).mean()), rel=1e-10)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("node", [0, 63, 64, 70 * 9 * 33 - 1])
+def test_one_node_that_is_not_finite_is_reported(orc, bad, node):
+    shape = (70, 9, 33)
+    f = orc.init_feq(inputs.smooth_random(shape, 0.05, seed=3))
+    f.reshape(27, -1)[13, node] = bad      # the population at rest: the velocity may stay finite
+    with kbc.Box(shape, 2e-3) as b:
+        b.set_populations(f)
+        for call in (b.energy, b.moments, b.enstrophy):
+            with pytest.raises(kbc.KbcError) as e:
+                call()
+            assert e.value.code == kbc.KBC_EUNSTABLE
