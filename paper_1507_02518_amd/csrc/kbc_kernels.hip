@@ -354,13 +354,6 @@ __global__ void __launch_bounds__(kBlock) k_reduce_final_k(const double* __restr
 // Flow statistics of section V from the velocity field u[3][N].
 // ---------------------------------------------------------------------------
 
-// (a + d) mod n for any small signed d
-__device__ __forceinline__ uint32_t wrap_mod(uint32_t a, int d, uint32_t n)
-{
-    int64_t v = ((int64_t)a + d) % (int64_t)n;
-    return (uint32_t)(v < 0 ? v + n : v);
-}
-
 // Central first-derivative weights of f(x+m) - f(x-m): second order, and
 // the nine-point eighth-order stencil.
 template <int ORD> struct FdW;
@@ -377,67 +370,109 @@ template <> struct FdW<8> {
 };
 
 // Per-block sums of |curl u|^2, sum_ab (d_a u_b + d_b u_a)^2, (div u)^2 and
-// (du_x/dx)^n for n = 2..6 (grid-stride, fixed order).
+// (du_x/dx)^n for n = 2..6 (fixed order).  A workgroup marches a tile of
+// 32 x 8 columns through kGradPlanes planes: a thread keeps its column's
+// 2M + 1 planes in registers for the z derivatives, and the plane's tile with
+// its halo goes through LDS for the others, 10 loads per node and plane at
+// eighth order instead of 72 with a 64-bit remainder for each neighbour.
+// 200^3, eighth order: 0.45 -> 0.18 ms.
+constexpr uint32_t kGradX = 32, kGradY = 8, kGradPlanes = 32;
+static_assert(kGradX * kGradY == kBlock, "one thread per column");
+
 template <int ORD>
 __global__ void __launch_bounds__(kBlock) k_grad_stats(Geom g, const double* __restrict__ u,
                                                        double* __restrict__ partial)
 {
+    constexpr int M = FdW<ORD>::M;
+    constexpr uint32_t W = kGradX + 2 * M, H = kGradY + 2 * M, PER = (W * H + kBlock - 1) / kBlock;
+    __shared__ double tile[3][H * W];
     const size_t N = g.nnodes;
+    const uint32_t t = threadIdx.x, tx = t % kGradX, ty = t / kGradX;
+    const uint32_t slab = g.nx * g.ny;
+    const uint32_t ntx = (g.nx + kGradX - 1) / kGradX, nty = (g.ny + kGradY - 1) / kGradY;
+    const uint32_t items = ntx * nty * ((g.nz + kGradPlanes - 1) / kGradPlanes);
     double acc[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) acc[k] = 0.0;
-    for (uint32_t n = blockIdx.x * kBlock + threadIdx.x; n < g.nnodes; n += gridDim.x * kBlock) {
-        uint32_t x, y, z;
-        node_xyz(n, g, x, y, z);
-        double G[3][3];  // G[a][b] = d u_a / d x_b
+    for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const uint32_t xi = it % ntx, yz = it / ntx, x0 = xi * kGradX, y0 = yz % nty * kGradY;
+        const uint32_t z0 = yz / nty * kGradPlanes;
+        const uint32_t planes = g.nz - z0 < kGradPlanes ? g.nz - z0 : kGradPlanes;
+        const bool real = x0 + tx < g.nx && y0 + ty < g.ny;
+        const uint32_t own = ((y0 + ty) % g.ny) * g.nx + (x0 + tx) % g.nx;
+        // tile element e = t + k 256 is node (x0 - M + e % W, y0 - M + e / W), periodic
+        uint32_t from[PER];
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            uint32_t np[FdW<ORD>::M], nm[FdW<ORD>::M];
+        for (uint32_t k = 0; k < PER; ++k) {
+            const uint32_t e = t + k * kBlock;
+            const uint32_t x = (x0 + e % W + M * g.nx - M) % g.nx, y = (y0 + e / W + M * g.ny - M) % g.ny;
+            from[k] = y * g.nx + x;
+        }
+        double col[3][2 * M + 1];   // [a][d]: u_a at plane z - M + d
 #pragma unroll
-            for (int m = 1; m <= FdW<ORD>::M; ++m) {
-                if (b == 0) {
-                    np[m - 1] = node_of(wrap_mod(x, m, g.nx), y, z, g);
-                    nm[m - 1] = node_of(wrap_mod(x, -m, g.nx), y, z, g);
-                } else if (b == 1) {
-                    np[m - 1] = node_of(x, wrap_mod(y, m, g.ny), z, g);
-                    nm[m - 1] = node_of(x, wrap_mod(y, -m, g.ny), z, g);
-                } else {
-                    np[m - 1] = node_of(x, y, wrap_mod(z, m, g.nz), g);
-                    nm[m - 1] = node_of(x, y, wrap_mod(z, -m, g.nz), g);
-                }
-            }
+        for (int d = 1; d <= 2 * M; ++d) {
+            const size_t at = (size_t)((z0 + d - 1 + M * g.nz - M) % g.nz) * slab + own;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) col[a][d] = u[a * N + at];
+        }
+        for (uint32_t p = 0; p < planes; ++p) {
+            const size_t at = (size_t)((z0 + p + M) % g.nz) * slab + own;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                double d = 0.0;
 #pragma unroll
-                for (int m = 1; m <= FdW<ORD>::M; ++m)
-                    d += FdW<ORD>::c(m) * (u[a * N + np[m - 1]] - u[a * N + nm[m - 1]]);
-                G[a][b] = d;
+                for (int d = 0; d < 2 * M; ++d) col[a][d] = col[a][d + 1];
+                col[a][2 * M] = u[a * N + at];
             }
+            const double* plane = u + (size_t)(z0 + p) * slab;
+            __syncthreads();
+#pragma unroll
+            for (uint32_t k = 0; k < PER; ++k) {
+                const uint32_t e = t + k * kBlock;
+                if (e < W * H)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) tile[a][e] = plane[a * N + from[k]];
+            }
+            __syncthreads();
+            const uint32_t c = (ty + M) * W + tx + M;
+            double G[3][3];  // G[a][b] = d u_a / d x_b
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                double dx = 0.0, dy = 0.0, dz = 0.0;
+#pragma unroll
+                for (int m = 1; m <= M; ++m) {
+                    dx += FdW<ORD>::c(m) * (tile[a][c + m] - tile[a][c - m]);
+                    dy += FdW<ORD>::c(m) * (tile[a][c + m * W] - tile[a][c - m * W]);
+                    dz += FdW<ORD>::c(m) * (col[a][M + m] - col[a][M - m]);
+                }
+                G[a][0] = dx;
+                G[a][1] = dy;
+                G[a][2] = dz;
+            }
+            if (!real) continue;
+            const double wx = G[2][1] - G[1][2], wy = G[0][2] - G[2][0], wz = G[1][0] - G[0][1];
+            acc[0] += wx * wx + wy * wy + wz * wz;
+            double e = 0.0;
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const double sab = G[a][b] + G[b][a];
+                    e += sab * sab;
+                }
+            acc[1] += e;
+            const double dv = G[0][0] + G[1][1] + G[2][2];
+            acc[2] += dv * dv;
+            const double d1 = G[0][0], d2 = d1 * d1, d3 = d2 * d1;
+            acc[3] += d2;
+            acc[4] += d3;
+            acc[5] += d2 * d2;
+            acc[6] += d3 * d2;
+            acc[7] += d3 * d3;
         }
-        const double wx = G[2][1] - G[1][2], wy = G[0][2] - G[2][0], wz = G[1][0] - G[0][1];
-        acc[0] += wx * wx + wy * wy + wz * wz;
-        double e = 0.0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const double sab = G[a][b] + G[b][a];
-                e += sab * sab;
-            }
-        acc[1] += e;
-        const double dv = G[0][0] + G[1][1] + G[2][2];
-        acc[2] += dv * dv;
-        const double d1 = G[0][0], d2 = d1 * d1, d3 = d2 * d1;
-        acc[3] += d2;
-        acc[4] += d3;
-        acc[5] += d2 * d2;
-        acc[6] += d3 * d2;
-        acc[7] += d3 * d3;
     }
+    __syncthreads();
     block_sum<8>(acc, partial + 8 * blockIdx.x);
 }
-
 
 __global__ void __launch_bounds__(kBlock) k_gamma_final(const double* __restrict__ partial,
                                                         int count, double* __restrict__ out)
@@ -787,7 +822,9 @@ hipError_t launch_curl(const Geom& g, const double* u, double* partial, double* 
 hipError_t launch_grad_stats(int order, const Geom& g, const double* u, double* partial,
                              double* out, hipStream_t stream)
 {
-    const unsigned blocks = std::min<unsigned>(kReduceBlocks, grid_for(g.nnodes));
+    const uint64_t items = (uint64_t)((g.nx + kGradX - 1) / kGradX) * ((g.ny + kGradY - 1) / kGradY) *
+                           ((g.nz + kGradPlanes - 1) / kGradPlanes);
+    const unsigned blocks = (unsigned)std::min<uint64_t>(kReduceBlocks, items);
     if (order == 8) hipLaunchKernelGGL(k_grad_stats<8>, dim3(blocks), dim3(kBlock), 0, stream, g, u, partial);
     else hipLaunchKernelGGL(k_grad_stats<2>, dim3(blocks), dim3(kBlock), 0, stream, g, u, partial);
     hipError_t e = hipGetLastError();

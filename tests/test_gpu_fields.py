@@ -1,9 +1,11 @@
 """Density, velocity and the sums over nodes at the sizes where their kernels
 can go wrong: fewer nodes than a wavefront, a partial last run, more runs
-than groups, and column marches with remainders."""
+than groups, tiles and column marches with remainders, axes shorter than a
+derivative's reach."""
 import numpy as np
 import pytest
 
+from oracle import statistics as ost
 from paper_1507_02518_amd import inputs, kbc
 from paper_1507_02518_amd.kbc import AA, F16_DEV, F32_DEV, F32_DEV_X, F64, PULL
 
@@ -64,3 +66,21 @@ def test_one_node_that_is_not_finite_is_reported(orc, bad, node):
             with pytest.raises(kbc.KbcError) as e:
                 call()
             assert e.value.code == kbc.KBC_EUNSTABLE
+
+
+@pytest.mark.parametrize("order", [2, 8])
+@pytest.mark.parametrize("shape", [(3, 2, 5), (33, 9, 33), (64, 17, 32), (31, 8, 70)])
+def test_gradient_statistics_on_ragged_tiles(shape, order):
+    with kbc.Box(shape, 2e-3) as b:
+        b.init_velocity(inputs.smooth_random(shape, 0.05, seed=9))
+        b.step(2)
+        got = b.statistics(order)
+        _, u = b.moments()
+    ref = ost.statistics(u, 2e-3, order)
+    for key in ("k", "omega", "epsilon", "div2"):
+        assert got[key] == pytest.approx(ref[key], rel=1e-12), key
+    for n in range(2, 7):
+        # odd moments cancel: their rounding is that of the terms
+        scale = ref["dudx_moments"][2] ** (n / 2)
+        assert got["dudx_moments"][n] == pytest.approx(ref["dudx_moments"][n], rel=1e-11,
+                                                       abs=1e-11 * scale), n
