@@ -511,67 +511,120 @@ __global__ void __launch_bounds__(kBlock) k_gamma_final(const double* __restrict
     }
 }
 
-// Sums over the (y, z) lines of u'_c(x) u'_c(x + r) for c = x, y components
-// and r = 0..rmax.  A block stages one line at a time in LDS; thread t owns
-// the lags r = t, t + kBlock, ... (at most kCorrLags per thread) for all the
-// lines the block visits, so the per-block sums come out in a fixed order.
-constexpr int kCorrLags = 8;
+// Sums over the (y, z) lines of u'_c(x) u'_c(x + r) for the components c = x, y
+// and r = 0..rmax.  A workgroup stages kCorrLines lines of one component in
+// LDS, each followed by its own start (so that x + r needs no wrap) and padded
+// by one value in eight, and splits the products into tiles of 8 nodes x 8
+// lags: 23 reads from LDS for 64 multiply-adds in registers, where one lag per
+// thread and pass read two values for each.  Thread t has lags
+// 8 (t mod lag_tiles) .. + 7 and the node tiles t / lag_tiles, + groups, ...;
+// the padding puts the windows of neighbouring lag tiles 9 values apart, on
+// different banks.  Bound by the FP64 multiply-adds and the LDS reads beside
+// them: 200^3 with 101 lags 0.77 -> 0.15 ms.
 constexpr int kCorrMaxN = 4096;
+constexpr int kCorrMaxLags = 2048;
+constexpr int kCorrTile = 8;
+constexpr int kCorrBlocks = 1024;   // workgroups per component and lag range
+__host__ __device__ constexpr uint32_t corr_pad(uint32_t i) { return i + i / 8; }
 
-__global__ void __launch_bounds__(kBlock) k_corr_x(Geom g, const double* __restrict__ u,
+// Lag tiles of one workgroup, at most (more lags: further workgroups).
+constexpr uint32_t kCorrLagTiles = 64;
+
+struct CorrPlan {
+    uint32_t lag_tiles;   // of one workgroup
+    uint32_t ranges;      // lag ranges
+    uint32_t lines;       // staged at a time
+    uint32_t stride;      // LDS values per line
+    uint32_t blocks;      // per component and range
+};
+
+inline CorrPlan corr_plan(const Geom& g, int rmax)
+{
+    CorrPlan p;
+    const uint32_t tiles = (uint32_t)rmax / kCorrTile + 1;
+    p.ranges = (tiles + kCorrLagTiles - 1) / kCorrLagTiles;
+    p.lag_tiles = (tiles + p.ranges - 1) / p.ranges;
+    // a line, its start again up to the last window's end
+    p.stride = corr_pad(g.nx + p.ranges * p.lag_tiles * kCorrTile + 2 * kCorrTile) + 1;
+    // several short lines at a time keep the threads' shares even; 32 KB
+    p.lines = std::max<uint32_t>(1, std::min<uint32_t>(8, 4096 / p.stride));
+    p.blocks = (uint32_t)std::min<uint64_t>(kCorrBlocks, ((uint64_t)g.ny * g.nz + p.lines - 1) / p.lines);
+    return p;
+}
+
+__global__ void __launch_bounds__(kBlock) k_corr_x(Geom g, CorrPlan p, const double* __restrict__ u,
                                                    const double* __restrict__ mean_sum, int rmax,
                                                    double* __restrict__ partial)
 {
-    __shared__ double line[2][kCorrMaxN];
+    extern __shared__ double line[];
+    const uint32_t comp = blockIdx.y, range = blockIdx.z, t = threadIdx.x;
     const size_t N = g.nnodes;
-    const double mx = mean_sum[0] / (double)N, my = mean_sum[1] / (double)N;
-    double acc[2][kCorrLags];
+    const double mean = mean_sum[comp] / (double)N;
+    const double* uc = u + comp * N;
+    const uint32_t lines = g.ny * g.nz, groups = kBlock / p.lag_tiles;
+    const uint32_t lt = t % p.lag_tiles, grp = t / p.lag_tiles;
+    const uint32_t lag0 = (range * p.lag_tiles + lt) * kCorrTile;
+    const uint32_t full = g.nx / kCorrTile, tail = g.nx % kCorrTile;
+    const uint32_t ext = g.nx + p.ranges * p.lag_tiles * kCorrTile + 2 * kCorrTile;
+    double acc[kCorrTile];
 #pragma unroll
-    for (int k = 0; k < kCorrLags; ++k) acc[0][k] = acc[1][k] = 0.0;
-    const uint32_t lines = g.ny * g.nz;
-    for (uint32_t l = blockIdx.x; l < lines; l += gridDim.x) {
-        const size_t base = (size_t)l * g.nx;
+    for (int k = 0; k < kCorrTile; ++k) acc[k] = 0.0;
+    for (uint32_t l0 = blockIdx.x * p.lines; l0 < lines; l0 += gridDim.x * p.lines) {
+        const uint32_t here = lines - l0 < p.lines ? lines - l0 : p.lines;
         __syncthreads();
-        for (uint32_t x = threadIdx.x; x < g.nx; x += kBlock) {
-            line[0][x] = u[base + x] - mx;
-            line[1][x] = u[N + base + x] - my;
+        for (uint32_t l = 0; l < here; ++l) {
+            const double* src = uc + (size_t)(l0 + l) * g.nx;
+            for (uint32_t i = t; i < ext; i += kBlock) line[l * p.stride + corr_pad(i)] = src[i % g.nx] - mean;
         }
         __syncthreads();
+        if (grp < groups) {
+            for (uint32_t it = grp; it < here * full; it += groups) {
+                const uint32_t l = it / full, xt = it - l * full;
+                // tiles start at multiples of 8: element k of a window is k + k / 8 on
+                const double* a = line + l * p.stride + corr_pad(xt * kCorrTile);
+                const double* b = line + l * p.stride + corr_pad(xt * kCorrTile + lag0);
+                double av[8], bv[15];
 #pragma unroll
-        for (int k = 0; k < kCorrLags; ++k) {
-            const int r = threadIdx.x + k * kBlock;
-            if (r > rmax) break;
-            double s0 = 0.0, s1 = 0.0;
-            uint32_t xr = (uint32_t)r % g.nx;
-            for (uint32_t x = 0; x < g.nx; ++x) {
-                s0 += line[0][x] * line[0][xr];
-                s1 += line[1][x] * line[1][xr];
-                xr = xr + 1 == g.nx ? 0u : xr + 1;
+                for (int k = 0; k < 8; ++k) av[k] = a[k];
+#pragma unroll
+                for (int k = 0; k < 15; ++k) bv[k] = b[k + k / 8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) acc[k] = fma(av[i], bv[i + k], acc[k]);
             }
-            acc[0][k] += s0;
-            acc[1][k] += s1;
+            // the nodes past the last whole tile, one at a time
+            for (uint32_t it = grp; it < here * tail; it += groups) {
+                const uint32_t l = it / tail, x = full * kCorrTile + it - l * tail;
+                const double av = line[l * p.stride + corr_pad(x)];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) acc[k] = fma(av, line[l * p.stride + corr_pad(x + lag0 + k)], acc[k]);
+            }
         }
     }
-    const int L = rmax + 1;
+    // over the groups, in order
+    __syncthreads();
+    if (grp < groups)
 #pragma unroll
-    for (int k = 0; k < kCorrLags; ++k) {
-        const int r = threadIdx.x + k * kBlock;
-        if (r < L) {
-            partial[((size_t)blockIdx.x * L + r) * 2] = acc[0][k];
-            partial[((size_t)blockIdx.x * L + r) * 2 + 1] = acc[1][k];
-        }
+        for (int k = 0; k < 8; ++k) line[(grp * p.lag_tiles + lt) * 8 + k] = acc[k];
+    __syncthreads();
+    for (uint32_t k = t; k < p.lag_tiles * 8; k += kBlock) {
+        const uint32_t lag = range * p.lag_tiles * 8 + k;
+        if (lag > (uint32_t)rmax) continue;
+        double s = 0.0;
+        for (uint32_t q = 0; q < groups; ++q) s += line[q * p.lag_tiles * 8 + k];
+        partial[((size_t)lag * 2 + comp) * gridDim.x + blockIdx.x] = s;   // [2r + c][block]
     }
 }
 
+// out[2r + c] from the workgroups' sums, one workgroup each.
 __global__ void __launch_bounds__(kBlock) k_corr_final(const double* __restrict__ partial,
-                                                       int blocks, int rmax, double* __restrict__ out)
+                                                       int blocks, double* __restrict__ out)
 {
-    const int L = rmax + 1;
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= 2 * L) return;
-    double s = 0.0;
-    for (int b = 0; b < blocks; ++b) s += partial[(size_t)b * 2 * L + t];
-    out[t] = s;  // out[2r + c]
+    const double* p = partial + (size_t)blockIdx.x * blocks;
+    double acc[1] = {0.0};
+    for (int b = threadIdx.x; b < blocks; b += kBlock) acc[0] += p[b];
+    block_sum<1>(acc, out + blockIdx.x);
 }
 
 inline unsigned grid_for(uint32_t n) { return (n + kBlock - 1) / kBlock; }
@@ -857,22 +910,24 @@ hipError_t launch_gamma_stats(int storage, int variant, bool exact_gamma, int la
 }
 
 int corr_max_nx() { return kCorrMaxN; }
-int corr_max_lags() { return kCorrLags * kBlock; }
+int corr_max_lags() { return kCorrMaxLags; }
 size_t corr_partials(const Geom& g, int rmax)
 {
-    return (size_t)std::min<uint32_t>(kReduceBlocks, g.ny * g.nz) * 2 * (rmax + 1);
+    return (size_t)corr_plan(g, rmax).blocks * 2 * (rmax + 1);
 }
 
 hipError_t launch_corr_x(const Geom& g, const double* u, const double* mean_sum, int rmax,
                          double* partial, double* out, hipStream_t stream)
 {
-    const int blocks = (int)std::min<uint32_t>(kReduceBlocks, g.ny * g.nz);
-    hipLaunchKernelGGL(k_corr_x, dim3(blocks), dim3(kBlock), 0, stream, g, u, mean_sum, rmax, partial);
+    const CorrPlan p = corr_plan(g, rmax);
+    const size_t reduce = (size_t)(kBlock / p.lag_tiles) * p.lag_tiles * 8;
+    const size_t lds = std::max<size_t>((size_t)p.lines * p.stride, reduce) * sizeof(double);
+    hipLaunchKernelGGL(k_corr_x, dim3(p.blocks, 2, p.ranges), dim3(kBlock), lds, stream, g, p, u,
+                       mean_sum, rmax, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int L2 = 2 * (rmax + 1);
-    hipLaunchKernelGGL(k_corr_final, dim3((L2 + kBlock - 1) / kBlock), dim3(kBlock), 0, stream,
-                       partial, blocks, rmax, out);
+    hipLaunchKernelGGL(k_corr_final, dim3(2 * (rmax + 1)), dim3(kBlock), 0, stream, partial,
+                       (int)p.blocks, out);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Density, velocity and the sums over nodes at the sizes where their kernels
 can go wrong: fewer nodes than a wavefront, a partial last run, more runs
 than groups, tiles and column marches with remainders, axes shorter than a
-derivative's reach."""
+derivative's reach, and every lag tiling of the x-correlation."""
 import numpy as np
 import pytest
 
@@ -84,3 +84,17 @@ def test_gradient_statistics_on_ragged_tiles(shape, order):
         scale = ref["dudx_moments"][2] ** (n / 2)
         assert got["dudx_moments"][n] == pytest.approx(ref["dudx_moments"][n], rel=1e-11,
                                                        abs=1e-11 * scale), n
+
+
+@pytest.mark.parametrize("shape,rmax", [
+    ((1, 5, 3), 0), ((5, 3, 2), 4), ((13, 70, 3), 12), ((40, 12, 10), 0), ((64, 16, 130), 7),
+    ((64, 16, 5), 8), ((600, 3, 2), 599), ((1100, 2, 1), 1030)])
+def test_correlation_tilings_match_oracle(shape, rmax):
+    with kbc.Box(shape, 2e-3) as b:
+        u0 = inputs.smooth_random(shape, 0.05, seed=21)
+        b.init_velocity(u0)
+        b.step(1)
+        r11, r22 = b.correlation(rmax)
+        _, u = b.moments()
+    o11, o22 = ost.correlation_x(u, rmax)
+    assert np.abs(r11 - o11).max() < 1e-13 and np.abs(r22 - o22).max() < 1e-13
