@@ -214,6 +214,12 @@ int read_sums(kbc_handle h, double* s, int n)
 #define KBC_STEP_GRAPH 16
 #endif
 constexpr int kStepGraph = KBC_STEP_GRAPH;
+
+// kbc_energy_series adds up the sums of this many states at once, fewer where
+// their scratch would pass kSeriesBytes (0.63 B per node and state): the two
+// launches for it take 15 us, the step itself 7 us on the smallest boxes.
+constexpr int64_t kSeriesBatch = 16;
+constexpr int64_t kSeriesBytes = 32 << 20;
 static_assert(kStepGraph % 4 == 0, "a graph must return the box to its start state");
 
 void drop_graph(kbc_handle h)
@@ -367,6 +373,17 @@ int step_once(kbc_handle h)
     StepParams p = step_params(h);
     const int sweep = step_sweep(h, h->cur, h->t, p);
     KBC_HIP(launch_step(h->dtype, h->variant, sweep, h->exact_gamma, p, h->stream));
+    if (h->streaming == KBC_PULL) h->cur = 1 - h->cur;
+    h->t += 1;
+    return KBC_OK;
+}
+
+// A step that leaves the energy sums of the state it reads in `runs`.
+int step_series(kbc_handle h, double* runs)
+{
+    StepParams p = step_params(h);
+    const int sweep = step_sweep(h, h->cur, h->t, p);
+    KBC_HIP(launch_step_series(h->dtype, h->variant, sweep, p, runs, h->stream));
     if (h->streaming == KBC_PULL) h->cur = 1 - h->cur;
     h->t += 1;
     return KBC_OK;
@@ -652,16 +669,34 @@ int kbc_energy_series(kbc_handle h, int64_t n, double* k)
     if (n == 0) return KBC_OK;
     if (int r = set_device(h)) return r;
     if (int r = ensure_small(h)) return r;
-    double* d_log = nullptr;   // sum of |u - <u>|^2 after each step
-    KBC_HIP(hipMalloc(&d_log, (size_t)n * sizeof(double)));
-    // d_sum[6] counts the nodes that were not finite over the n passes
+    // The sums of a state come from the step that reads it next, those of
+    // several states being added up at once (two small launches), and the last
+    // state's from a pass of its own.  The exact stabilizer's step is bound by
+    // arithmetic and its registers are full: a pass after each step.
+    const bool fused = !h->exact_gamma && n > 1;
+    const size_t runs = series_partials(h->g);
+    const int64_t batch =
+        std::min<int64_t>(n - 1, std::max<int64_t>(1, std::min<int64_t>(kSeriesBatch, (int64_t)(kSeriesBytes / (8 * runs)))));
+    double* d_log = nullptr;   // sum of |u - <u>|^2 after each step, then scratch
+    KBC_HIP(hipMalloc(&d_log, ((size_t)n + (fused ? (runs + energy_partials()) * batch : 0)) * sizeof(double)));
+    double* groups = d_log + n;
+    double* d_runs = groups + (size_t)energy_partials() * batch;
+    // d_sum[6]: some node was not finite in the n states
     hipError_t e = hipMemsetAsync(h->d_sum + 6, 0, sizeof(double), h->stream);
     int r = e == hipSuccess ? KBC_OK : hip_fail(e, "hipMemsetAsync");
+    int64_t held = 0;   // states whose sums wait in d_runs
     for (int64_t j = 0; j < n && r == KBC_OK; ++j) {
-        r = kbc_step(h, 1);
+        const bool from_step = fused && j > 0;   // this step takes the sums of state j - 1
+        r = from_step ? step_series(h, d_runs + runs * held) : step_once(h);
         if (r != KBC_OK) break;
-        e = launch_fields(h->dtype, layout_now(h), state_buf(h), h->g, h->inv_scale, nullptr,
-                          nullptr, h->d_partial, h->d_sum, d_log + j, h->stream);
+        held += from_step;
+        if (held > 0 && (held == batch || j == n - 1)) {
+            e = launch_series_sums(h->g, (int)held, d_runs, groups, h->d_sum, d_log + j - held, h->stream);
+            held = 0;
+        }
+        if (e == hipSuccess && (!fused || j == n - 1))
+            e = launch_fields(h->dtype, layout_now(h), state_buf(h), h->g, h->inv_scale, nullptr,
+                              nullptr, h->d_partial, h->d_sum, d_log + j, h->stream);
         if (e != hipSuccess) r = hip_fail(e, "kbc_energy_series");
     }
     double bad = 0.0;

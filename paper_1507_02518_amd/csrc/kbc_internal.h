@@ -201,11 +201,22 @@ hipError_t launch_sample_pop(int storage, int layout, const void* buf, const Geo
 // and out[0..2] = sum_x u_a(x), out[3] = sum_x |u(x) - <u>|^2, out[4] = nodes
 // where a value is not finite; the same bits whether u is stored or not.
 // partial: device scratch of energy_partials() doubles; with
-// log (may be NULL) it receives out[3], and out[4] is added to out[6].
+// log (may be NULL) it receives out[3], and out[6] becomes 1 if out[4] is not 0.
 int energy_partials();
 hipError_t launch_fields(int storage, int layout, const void* buf, const Geom& g,
                          const float* inv_scale, double* rho, double* u, double* partial,
                          double* out, double* log, hipStream_t stream);
+
+// A step (estimate gamma only) that also leaves the sums of the state it reads in
+// `runs`, series_partials(g) doubles, and the sums over `count` such arrays, one
+// after the other: what launch_fields writes to log for each state goes to
+// log[0 .. count), and out[6] becomes 1 if some node was not finite.
+// groups: count * energy_partials() doubles.
+size_t series_partials(const Geom& g);
+hipError_t launch_step_series(int storage, int variant, int sweep, const StepParams& p,
+                              double* runs, hipStream_t stream);
+hipError_t launch_series_sums(const Geom& g, int count, const double* runs, double* groups,
+                              double* out, double* log, hipStream_t stream);
 
 // Plain streaming copy of n16 16-byte words.
 hipError_t launch_copy16(void* dst, const void* src, size_t n16, hipStream_t stream);
@@ -287,6 +298,7 @@ struct LoadCtx {
     float inv_scale[27];
 };
 using PoolFn = void (*)(const PoolBox*, const uint32_t*, const PoolMeta*, int);
+using SeriesFn = void (*)(StepParams, double*);
 using GammaFn = void (*)(int, const void*, Geom, Coll, LoadCtx, double*);
 
 // c64: the box is x-blocked in chunks of 64 nodes (a pull sweep may then
@@ -297,6 +309,8 @@ template <int S>
 PairFn pair_kernel(int variant);               // FP64 and FP32 dev, estimate gamma only
 template <int S>
 PoolFn pool_kernel(int variant, int sweep, bool one);   // estimate gamma only
+template <int S>
+SeriesFn series_kernel(int variant, int sweep, bool c64);   // estimate gamma only
 template <int S, bool GX>
 GammaFn gamma_kernel(int variant);
 

@@ -227,9 +227,29 @@ __device__ __forceinline__ double group_count(uint32_t w, uint32_t nnodes)
     return 64.0 * mine - ((runs - 1) % waves == w ? 64.0 * runs - (double)nnodes : 0.0);
 }
 
+// The groups' sums from the runs' of blockIdx.y-th state, one thread each (the
+// adding that k_fields does as it goes).
+__global__ void __launch_bounds__(kBlock) k_energy_groups(const EnergySum* __restrict__ runs_of,
+                                                          uint32_t nnodes,
+                                                          EnergySum* __restrict__ groups)
+{
+    const uint32_t runs = (nnodes + 63) / 64, waves = runs < kEnergyGroups ? runs : kEnergyGroups;
+    const uint32_t w = blockIdx.x * kBlock + threadIdx.x;
+    if (w >= waves) return;
+    runs_of += (size_t)blockIdx.y * runs;
+    EnergyAcc acc;
+    for (uint32_t j = w; j < runs; j += waves) {
+        double inv;
+        const double count = run_count(j, nnodes, inv);
+        add_energy(acc, runs_of[j], count, inv, j == w);
+    }
+    groups[(size_t)blockIdx.y * kEnergyGroups + w] = total_energy(acc);
+}
+
 // The sums over all nodes from the groups': out[0..2] sum of u, [3] sum of
-// |u - <u>|^2, [4] nodes that are not finite.  log (may be NULL) takes out[3] of
-// this step, and out[6] then counts on.  One workgroup; every thread adds its
+// |u - <u>|^2, [4] nodes that are not finite.  log (may be NULL) takes out[3],
+// and out[6] then becomes 1 if some node was not finite.  One workgroup for each
+// of gridDim.x states, the last of which fills out; every thread adds its
 // groups to the deviations from the first group's mean, and the five sums
 // are then plain ones.
 constexpr int kFinalBlock = 1024;
@@ -240,6 +260,7 @@ __global__ void __launch_bounds__(kFinalBlock) k_energy_final(const EnergySum* _
 {
 #pragma clang fp contract(off)
     __shared__ double part[kFinalBlock / 64][5];
+    groups += (size_t)blockIdx.x * kEnergyGroups;
     const uint32_t runs = (nnodes + 63) / 64, waves = runs < kEnergyGroups ? runs : kEnergyGroups;
     const double r0 = 1.0 / group_count(0, nnodes);
     const double c[3] = {groups[0].s[0] * r0, groups[0].s[1] * r0, groups[0].s[2] * r0};
@@ -267,13 +288,15 @@ __global__ void __launch_bounds__(kFinalBlock) k_energy_final(const EnergySum* _
             for (int w = 1; w < kFinalBlock / 64; ++w) a[k] += part[w][k];
         }
         const double N = (double)nnodes;
-        for (int k = 0; k < 3; ++k) out[k] = N * c[k] + a[k];
         const double m2 = a[3] - ((a[0] * a[0] + a[1] * a[1]) + a[2] * a[2]) / N;
-        out[3] = m2;
-        out[4] = a[4];
+        if (blockIdx.x + 1 == gridDim.x) {
+            for (int k = 0; k < 3; ++k) out[k] = N * c[k] + a[k];
+            out[3] = m2;
+            out[4] = a[4];
+        }
         if (log) {
-            *log = m2;
-            out[6] += a[4];
+            log[blockIdx.x] = m2;
+            if (a[4] != 0.0) out[6] = 1.0;
         }
     }
 }
@@ -670,13 +693,18 @@ __global__ void __launch_bounds__(kBlock) k_rewrite16(u32x4* p, size_t n16, uint
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// x-blocked in chunks of 64 nodes (geom_blocked)
+static bool chunks_of_64(const Geom& g)
+{
+    return g.xshift == 6 && g.xmask == 63 && g.plane == 64 && g.chunk == 27 * 64;
+}
+
 hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gamma, const Geom& g,
                              StepFn* fn, uint32_t* grid, uint32_t* block)
 {
     // the AA kernels address populations in planes (see node_update)
     if (sweep != SW_PULL && !geom_is_planes(g)) return hipErrorInvalidValue;
-    // x-blocked in chunks of 64 nodes (geom_blocked)
-    const bool c64 = g.xshift == 6 && g.xmask == 63 && g.plane == 64 && g.chunk == 27 * 64;
+    const bool c64 = chunks_of_64(g);
     switch (storage) {
     case ST_F64: *fn = exact_gamma ? step_kernel<ST_F64, true>(variant, sweep, c64) : step_kernel<ST_F64, false>(variant, sweep, c64); break;
     case ST_F32: *fn = exact_gamma ? step_kernel<ST_F32, true>(variant, sweep, c64) : step_kernel<ST_F32, false>(variant, sweep, c64); break;
@@ -836,6 +864,40 @@ hipError_t launch_fields(int storage, int layout, const void* buf, const Geom& g
                                         : (u ? fields_kernel<ST_F16, true>(layout) : fields_kernel<ST_F16, false>(layout));
     hipLaunchKernelGGL(fn, grid, block, 0, stream, buf, g, lc, rho, u, groups);
     hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kFinalBlock), 0, stream, groups, g.nnodes, out, log);
+    return hipGetLastError();
+}
+
+size_t series_partials(const Geom& g)
+{
+    return ((uint64_t)g.nnodes + 63) / 64 * (sizeof(EnergySum) / sizeof(double));
+}
+
+hipError_t launch_step_series(int storage, int variant, int sweep, const StepParams& p,
+                              double* runs, hipStream_t stream)
+{
+    StepFn step;   // whose shape and chunks the series kernel takes
+    uint32_t grid, block;
+    hipError_t e = step_launch_shape(storage, variant, sweep, false, p.g, &step, &grid, &block);
+    if (e != hipSuccess) return e;
+    const bool c64 = chunks_of_64(p.g);
+    SeriesFn fn;
+    switch (storage) {
+    case ST_F64: fn = series_kernel<ST_F64>(variant, sweep, c64); break;
+    case ST_F32: fn = series_kernel<ST_F32>(variant, sweep, c64); break;
+    case ST_F32X: fn = series_kernel<ST_F32X>(variant, sweep, c64); break;
+    default: fn = series_kernel<ST_F16>(variant, sweep, c64); break;
+    }
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(block), 0, stream, p, runs);
+    return hipGetLastError();
+}
+
+hipError_t launch_series_sums(const Geom& g, int count, const double* runs, double* groups,
+                              double* out, double* log, hipStream_t stream)
+{
+    EnergySum* gr = reinterpret_cast<EnergySum*>(groups);
+    hipLaunchKernelGGL(k_energy_groups, dim3(kEnergyGroups / kBlock, count), dim3(kBlock), 0, stream,
+                       reinterpret_cast<const EnergySum*>(runs), g.nnodes, gr);
+    hipLaunchKernelGGL(k_energy_final, dim3(count), dim3(kFinalBlock), 0, stream, gr, g.nnodes, out, log);
     return hipGetLastError();
 }
 

@@ -81,10 +81,17 @@ typedef __attribute__((address_space(1))) char gchar_t;
 // at fixed byte distances that the loads and stores carry in their
 // immediate offset field where it reaches (FP16: all 27, 128 bytes apart)
 // instead of one scalar base per direction.
-template <int S, int V, int SW, bool GX = false, bool ALN = false, bool C64 = false>
+//
+// pre(f): called with the node's decoded populations before the collision.
+struct NoPre {
+    template <typename R>
+    __device__ __forceinline__ void operator()(R (&)[27]) const {}
+};
+
+template <int S, int V, int SW, bool GX = false, bool ALN = false, bool C64 = false, typename Pre = NoPre>
 __device__ __forceinline__ void node_update(const void* srcv, void* dstv, const Geom& g,
                                             const Coll& c, const int8_t* sexp, uint32_t n,
-                                            uint32_t n0 = 0, bool store = true)
+                                            uint32_t n0 = 0, bool store = true, Pre pre = Pre())
 {
     using T = typename Traits<S>::T;
     using R = typename Traits<S>::R;
@@ -170,6 +177,10 @@ __device__ __forceinline__ void node_update(const void* srcv, void* dstv, const 
         __builtin_amdgcn_sched_barrier(0);
     }
 
+    pre(f);
+    if constexpr (!ALN) {
+        if (!store) return;
+    }
     collide<S, V, GX>(f, c);
 
     // AA odd sweep: store offsets x + v are formed after the collision, from

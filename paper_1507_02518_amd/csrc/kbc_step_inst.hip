@@ -2,6 +2,7 @@
 // storage form and stabilizer mode.  The build compiles this file once per
 // pair (KBC_INST_STORAGE in {0, 1, 2, 3}, KBC_INST_EXACT in {0, 1}); the
 // launchers in kbc_kernels.hip reach the kernels through the tables below.
+#include "kbc_fields.h"
 #include "kbc_pair.h"
 #include "kbc_step.h"
 
@@ -34,6 +35,20 @@ StepFn step_of_sweep(int sw, bool c64)
     }
     return sw == SW_AA_EVEN ? k_step<kS, V, SW_AA_EVEN, kGX> : k_step<kS, V, SW_AA_ODD, kGX>;
 }
+
+#if !KBC_INST_EXACT
+template <int V>
+SeriesFn series_of_sweep(int sw, bool c64)
+{
+    if (sw == SW_PULL) {
+        if constexpr (kC64) {
+            if (c64) return k_series<kS, V, SW_PULL, true>;
+        }
+        return k_series<kS, V, SW_PULL>;
+    }
+    return sw == SW_AA_EVEN ? k_series<kS, V, SW_AA_EVEN> : k_series<kS, V, SW_AA_ODD>;
+}
+#endif
 
 template <int V>
 PoolFn pool_of_sweep(int sw, bool one)
@@ -98,6 +113,24 @@ PoolFn pool_kernel(int v, int sw, bool one)
 }
 
 template PoolFn pool_kernel<kS>(int, int, bool);
+
+template <int S>
+SeriesFn series_kernel(int v, int sw, bool c64)
+{
+    static_assert(S == kS, "instantiated for one storage form only");
+    switch (v) {
+    case V_D: return series_of_sweep<V_D>(sw, c64);
+    case V_DT: return series_of_sweep<V_DT>(sw, c64);
+    case V_DQ: return series_of_sweep<V_DQ>(sw, c64);
+    case V_CD: return series_of_sweep<V_CD>(sw, c64);
+    case V_CDT: return series_of_sweep<V_CDT>(sw, c64);
+    case V_CDQ: return series_of_sweep<V_CDQ>(sw, c64);
+    case V_CDTQ: return series_of_sweep<V_CDTQ>(sw, c64);
+    default: return series_of_sweep<V_DTQ>(sw, c64);
+    }
+}
+
+template SeriesFn series_kernel<kS>(int, int, bool);
 
 #if KBC_INST_STORAGE == 0 || KBC_INST_STORAGE == 1
 template <int S>

@@ -2,6 +2,8 @@
 can go wrong: fewer nodes than a wavefront, a partial last run, more runs
 than groups, tiles and column marches with remainders, axes shorter than a
 derivative's reach, and every lag tiling of the x-correlation."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -98,3 +100,44 @@ def test_correlation_tilings_match_oracle(shape, rmax):
         _, u = b.moments()
     o11, o22 = ost.correlation_x(u, rmax)
     assert np.abs(r11 - o11).max() < 1e-13 and np.abs(r22 - o22).max() < 1e-13
+
+
+@pytest.mark.parametrize("shape", [(5, 3, 2), (70, 9, 33), (48, 20, 36)])
+@pytest.mark.parametrize("n", [1, 2, 17, 20])
+@pytest.mark.parametrize("dtype,streaming,variant", [
+    (F64, PULL, kbc.S_DTQ), (F64, AA, kbc.S_CDT), (F32_DEV, PULL, kbc.S_DQ), (F32_DEV_X, AA, kbc.S_D),
+    (F16_DEV, AA, kbc.S_DTQ), (F16_DEV, PULL, kbc.S_CDTQ)])
+def test_series_is_the_energy_after_each_step(shape, n, dtype, streaming, variant):
+    _check_series(shape, n, dtype, streaming, variant)
+
+
+def test_series_with_fewer_states_at_once():
+    """A box large enough that its states are added up in smaller numbers."""
+    _check_series((192, 160, 132), 21, F32_DEV, AA, kbc.S_DTQ)
+
+
+def _check_series(shape, n, dtype, streaming, variant):
+    u = inputs.smooth_random(shape, 0.02, seed=3)
+    ks = np.empty(n)
+    with kbc.Box(shape, 2e-2, dtype, streaming=streaming, variant=variant) as b:
+        b.init_velocity(u)
+        b.step(1)
+        rc = kbc.load().kbc_energy_series(b.h, n, ks.ctypes.data_as(ctypes.POINTER(ctypes.c_double)))
+        t, f = b.t, b.populations()
+    kr = np.full(n, np.nan)     # where the state has left the range of FP16
+    with kbc.Box(shape, 2e-2, dtype, streaming=streaming, variant=variant) as b:
+        b.init_velocity(u)
+        b.step(1)
+        for j in range(n):
+            b.step(1)
+            try:
+                kr[j] = b.energy()
+            except kbc.KbcError as e:
+                assert e.code == kbc.KBC_EUNSTABLE
+        g = b.populations()
+    good = np.isfinite(kr)
+    assert dtype == F16_DEV or good.all()
+    assert rc == (kbc.KBC_OK if good.all() else kbc.KBC_EUNSTABLE)
+    # the same bits
+    assert t == n + 1 and np.array_equal(ks[good], kr[good])
+    assert np.array_equal(f, g, equal_nan=True)
