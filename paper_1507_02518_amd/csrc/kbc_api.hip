@@ -88,6 +88,7 @@ struct kbc_box {
     bool initialised;
     bool pairs;        // pull: two steps per launch (pair_plan)
     PairTiles tiles;
+    uint32_t threads;  // of a workgroup of the step (step_threads)
     bool xcd_eighths;  // AA sweeps with one eighth of the workgroups per XCD (step_block)
     // diagnostics scratch (allocated on first use)
     double* d_u;
@@ -295,14 +296,14 @@ int build_graph(kbc_handle h)
         } else {
             const int sweep = step_sweep(h, k % 2, k, p);
             StepFn fn;
-            uint32_t grid, block;
-            e = step_launch_shape(h->dtype, h->variant, sweep, h->exact_gamma, h->g, &fn, &grid,
-                                  &block);
+            uint32_t grid;
+            e = step_launch_shape(h->dtype, h->variant, sweep, h->exact_gamma, h->threads, h->g, &fn,
+                                  &grid);
             if (e != hipSuccess) break;
             args[0] = &p;
             np.func = reinterpret_cast<void*>(fn);
             np.gridDim = dim3(grid);
-            np.blockDim = dim3(block);
+            np.blockDim = dim3(h->threads);
         }
         np.sharedMemBytes = 0;
         np.kernelParams = args;
@@ -372,7 +373,7 @@ int step_once(kbc_handle h)
 {
     StepParams p = step_params(h);
     const int sweep = step_sweep(h, h->cur, h->t, p);
-    KBC_HIP(launch_step(h->dtype, h->variant, sweep, h->exact_gamma, p, h->stream));
+    KBC_HIP(launch_step(h->dtype, h->variant, sweep, h->exact_gamma, h->threads, p, h->stream));
     if (h->streaming == KBC_PULL) h->cur = 1 - h->cur;
     h->t += 1;
     return KBC_OK;
@@ -383,7 +384,7 @@ int step_series(kbc_handle h, double* runs)
 {
     StepParams p = step_params(h);
     const int sweep = step_sweep(h, h->cur, h->t, p);
-    KBC_HIP(launch_step_series(h->dtype, h->variant, sweep, p, runs, h->stream));
+    KBC_HIP(launch_step_series(h->dtype, h->variant, sweep, h->threads, p, runs, h->stream));
     if (h->streaming == KBC_PULL) h->cur = 1 - h->cur;
     h->t += 1;
     return KBC_OK;
@@ -513,14 +514,15 @@ int kbc_create(const int64_t shape[3], double nu, int32_t dtype, const kbc_optio
         }
         h->own_stream = true;
     }
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    h->threads = step_threads(h->exact_gamma, h->g.nnodes, (uint32_t)cus);
     // Boxes that take their steps in pairs: FP64 rows that 16 does not divide
     // are padded to whole 128-byte lines, where that costs at most an eighth
     // more memory (100^3: 76.6 -> 71.0 us per step in pairs, 86 in single
     // steps).
     if (opt.streaming == KBC_PULL) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-            cus = 256;
         h->pairs = pair_plan(dtype, opt.variant, h->exact_gamma, h->g, (uint32_t)cus, &h->tiles);
         const uint32_t pad = (16 - h->g.nx % 16) % 16;
         if (h->pairs && dtype == KBC_F64 && !geom_is_planes(h->g) && pad > 0 && 8 * pad <= h->g.nx &&

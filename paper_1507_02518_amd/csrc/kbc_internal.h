@@ -76,13 +76,28 @@ inline uint64_t geom_slot_span_bytes(const Geom& g, size_t elem)
 void set_last_error(const char* msg);
 
 // One time step of one box (src -> dst for pull; in place for AA).
-hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, const StepParams& p,
-                       hipStream_t stream);
+// block: step_threads().
+hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, uint32_t block,
+                       const StepParams& p, hipStream_t stream);
+
+// Threads of a workgroup of the step.  One wavefront for the exact stabilizer
+// (two waves per SIMD, and LDS for 64 threads: `collide`).  Otherwise 256, and
+// where fewer threads still give every CU no more than one workgroup, 128 or
+// 64, so that a small box spreads over all the CUs (us per step with 256 /
+// 128 / 64 threads, FP64 pull: 16^3 5.10 / 4.39 / 4.20, 32^3 6.48 / 4.88 /
+// 4.96; FP64 AA 32^3 7.32 / 5.38 / 5.56, FP32 AA 5.40 / 4.23 / 4.26).  Past that line
+// the larger workgroup is the better one or the same (FP32 pull 36^3 5.77 /
+// 6.19 / 6.58; 64 in the largest boxes 17-33% slower for the AA sweeps).
+inline uint32_t step_threads(bool exact_gamma, uint32_t nnodes, uint32_t cus)
+{
+    if (exact_gamma || nnodes <= 64 * cus) return 64;
+    return nnodes <= 128 * cus ? 128 : 256;
+}
 
 // The kernel and launch shape launch_step uses (for building graphs of steps).
 using StepFn = void (*)(StepParams);
-hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gamma, const Geom& g,
-                             StepFn* fn, uint32_t* grid, uint32_t* block);
+hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gamma, uint32_t block,
+                             const Geom& g, StepFn* fn, uint32_t* grid);
 
 // ---------------------------------------------------------------------------
 // Two steps of a pull box in one launch (k_pair, kbc_pair.h): a workgroup of
@@ -213,8 +228,8 @@ hipError_t launch_fields(int storage, int layout, const void* buf, const Geom& g
 // log[0 .. count), and out[6] becomes 1 if some node was not finite.
 // groups: count * energy_partials() doubles.
 size_t series_partials(const Geom& g);
-hipError_t launch_step_series(int storage, int variant, int sweep, const StepParams& p,
-                              double* runs, hipStream_t stream);
+hipError_t launch_step_series(int storage, int variant, int sweep, uint32_t block,
+                              const StepParams& p, double* runs, hipStream_t stream);
 hipError_t launch_series_sums(const Geom& g, int count, const double* runs, double* groups,
                               double* out, double* log, hipStream_t stream);
 

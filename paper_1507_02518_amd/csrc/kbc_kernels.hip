@@ -699,9 +699,11 @@ static bool chunks_of_64(const Geom& g)
     return g.xshift == 6 && g.xmask == 63 && g.plane == 64 && g.chunk == 27 * 64;
 }
 
-hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gamma, const Geom& g,
-                             StepFn* fn, uint32_t* grid, uint32_t* block)
+hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gamma, uint32_t block,
+                             const Geom& g, StepFn* fn, uint32_t* grid)
 {
+    // whole waves, and the threads the kernel was compiled for
+    if (block < 64 || block % 64 || block > (exact_gamma ? 64u : (uint32_t)kStepBlock)) return hipErrorInvalidValue;
     // the AA kernels address populations in planes (see node_update)
     if (sweep != SW_PULL && !geom_is_planes(g)) return hipErrorInvalidValue;
     const bool c64 = chunks_of_64(g);
@@ -711,21 +713,16 @@ hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gam
     case ST_F32X: *fn = exact_gamma ? step_kernel<ST_F32X, true>(variant, sweep, c64) : step_kernel<ST_F32X, false>(variant, sweep, c64); break;
     default: *fn = exact_gamma ? step_kernel<ST_F16, true>(variant, sweep, c64) : step_kernel<ST_F16, false>(variant, sweep, c64); break;
     }
-    // One wavefront per workgroup for the exact stabilizer (two waves per
-    // SIMD, and LDS for 64 threads: `collide`), kStepBlock threads otherwise (64 measured within
-    // +-2% for the other pull forms, 5% slower for FP16 pull, and 17-33%
-    // slower for the AA sweeps).
-    *block = exact_gamma ? 64u : (uint32_t)kStepBlock;
-    *grid = (g.nnodes + *block - 1) / *block;
+    *grid = (g.nnodes + block - 1) / block;
     return hipSuccess;
 }
 
-hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, const StepParams& p,
-                       hipStream_t stream)
+hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, uint32_t block,
+                       const StepParams& p, hipStream_t stream)
 {
     StepFn fn;
-    uint32_t grid, block;
-    hipError_t e = step_launch_shape(storage, variant, sweep, exact_gamma, p.g, &fn, &grid, &block);
+    uint32_t grid;
+    hipError_t e = step_launch_shape(storage, variant, sweep, exact_gamma, block, p.g, &fn, &grid);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fn, dim3(grid), dim3(block), 0, stream, p);
     return hipGetLastError();
@@ -872,12 +869,12 @@ size_t series_partials(const Geom& g)
     return ((uint64_t)g.nnodes + 63) / 64 * (sizeof(EnergySum) / sizeof(double));
 }
 
-hipError_t launch_step_series(int storage, int variant, int sweep, const StepParams& p,
-                              double* runs, hipStream_t stream)
+hipError_t launch_step_series(int storage, int variant, int sweep, uint32_t block,
+                              const StepParams& p, double* runs, hipStream_t stream)
 {
     StepFn step;   // whose shape and chunks the series kernel takes
-    uint32_t grid, block;
-    hipError_t e = step_launch_shape(storage, variant, sweep, false, p.g, &step, &grid, &block);
+    uint32_t grid;
+    hipError_t e = step_launch_shape(storage, variant, sweep, false, block, p.g, &step, &grid);
     if (e != hipSuccess) return e;
     const bool c64 = chunks_of_64(p.g);
     SeriesFn fn;
