@@ -89,6 +89,7 @@ struct kbc_box {
     bool pairs;        // pull: two steps per launch (pair_plan)
     PairTiles tiles;
     uint32_t threads;  // of a workgroup of the step (step_threads)
+    bool cached;       // steps store through the caches (cached_stores)
     bool xcd_eighths;  // AA sweeps with one eighth of the workgroups per XCD (step_block)
     // diagnostics scratch (allocated on first use)
     double* d_u;
@@ -290,15 +291,15 @@ int build_graph(kbc_handle h)
         if (h->pairs) {
             pp = pair_params(h, k % 2);
             args[0] = &pp;
-            np.func = reinterpret_cast<void*>(pair_step(h->dtype, h->variant));
+            np.func = reinterpret_cast<void*>(pair_step(h->dtype, h->variant, h->cached));
             np.gridDim = dim3(h->tiles.grid);
             np.blockDim = dim3(kPairBlock);
         } else {
             const int sweep = step_sweep(h, k % 2, k, p);
             StepFn fn;
             uint32_t grid;
-            e = step_launch_shape(h->dtype, h->variant, sweep, h->exact_gamma, h->threads, h->g, &fn,
-                                  &grid);
+            e = step_launch_shape(h->dtype, h->variant, sweep, h->exact_gamma, h->threads, h->cached,
+                                  h->g, &fn, &grid);
             if (e != hipSuccess) break;
             args[0] = &p;
             np.func = reinterpret_cast<void*>(fn);
@@ -373,7 +374,7 @@ int step_once(kbc_handle h)
 {
     StepParams p = step_params(h);
     const int sweep = step_sweep(h, h->cur, h->t, p);
-    KBC_HIP(launch_step(h->dtype, h->variant, sweep, h->exact_gamma, h->threads, p, h->stream));
+    KBC_HIP(launch_step(h->dtype, h->variant, sweep, h->exact_gamma, h->threads, h->cached, p, h->stream));
     if (h->streaming == KBC_PULL) h->cur = 1 - h->cur;
     h->t += 1;
     return KBC_OK;
@@ -394,7 +395,7 @@ int step_series(kbc_handle h, double* runs)
 int step_pair(kbc_handle h)
 {
     const PairParams p = pair_params(h, h->cur);
-    hipLaunchKernelGGL(pair_step(h->dtype, h->variant), dim3(h->tiles.grid), dim3(kPairBlock), 0,
+    hipLaunchKernelGGL(pair_step(h->dtype, h->variant, h->cached), dim3(h->tiles.grid), dim3(kPairBlock), 0,
                        h->stream, p);
     KBC_HIP(hipGetLastError());
     h->cur = 1 - h->cur;
@@ -531,6 +532,7 @@ int kbc_create(const int64_t shape[3], double nu, int32_t dtype, const kbc_optio
     }
     const size_t bytes = geom_extent(h->g) * elem_bytes(dtype);
     const int nbuf = h->streaming == KBC_PULL ? 2 : 1;
+    h->cached = cached_stores(h->streaming == KBC_PULL, nbuf * bytes);
     for (int b = 0; b < nbuf; ++b) {
         e = hipMalloc(&h->buf[b], bytes);
         if (e != hipSuccess) {

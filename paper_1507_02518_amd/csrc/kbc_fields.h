@@ -209,7 +209,7 @@ k_series(StepParams p, double* __restrict__ runs)
         for (int i = 0; i < 27; ++i) asm volatile("" : "+v"(f[i]));
     };
     constexpr bool ALN = SW == SW_AA_ODD && KBC_AA_ALIGNED && (S == ST_F64 || S == ST_F32X);
-    node_update<S, V, SW, false, ALN, C64>(p.src, p.dst, p.g, p.c, p.scale_exp,
+    node_update<S, V, SW, false, ALN, C64, false>(p.src, p.dst, p.g, p.c, p.scale_exp,
                                            real ? n : p.g.nnodes - 1, n0, real, pre);
 }
 

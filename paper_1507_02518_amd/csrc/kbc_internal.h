@@ -76,9 +76,31 @@ inline uint64_t geom_slot_span_bytes(const Geom& g, size_t elem)
 void set_last_error(const char* msg);
 
 // One time step of one box (src -> dst for pull; in place for AA).
-// block: step_threads().
+// block: step_threads(); cached: cached_stores().
 hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, uint32_t block,
-                       const StepParams& p, hipStream_t stream);
+                       bool cached, const StepParams& p, hipStream_t stream);
+
+// Whether a box's steps store through the caches instead of past them.  Stored
+// past them (non-temporal), a population that the next step reads comes from
+// the last-level cache or HBM, and where rows are no multiple of 128 bytes the
+// lines at the ends of a wave's run are written in parts; stored through them,
+// the lattice competes with the reads.  By the bytes of the box's lattices
+// (32 MB of L2, 256 MB of last-level cache; us per step, past / through):
+//   pull, more than the L2s and no more than the last-level cache: FP64 64^3
+//   (113 MB, in pairs) 21.5 / 18.3, 80^3 33.8 / 26.9, FP32 64^3 (57 MB) 12.3 / 10.3, 131 x
+//   97 x 61 (167 MB) 40.0 / 32.1, 104^3 (243 MB) 50.5 / 41.6;
+//   above: FP64 88^3 (294 MB) 48.8 / 50.3, 128^3 129 / 142, FP32 128^3 73.6 / 76.4;
+//   around the L2s' size: FP32 40^3 (14 MB) 6.3 / 6.9, 48^3 (24 MB) 7.9 / 9.0;
+//   far below it: FP64 16^3 4.20 / 3.95, FP32 24^3 (3 MB) 4.47 / 4.14.
+//   AA, more than the L2s: FP64 80^3 (110 MB) 44.2 / 39.8, 100^3 72.6 / 68.3,
+//   200^3 (1.7 GB) 705 / 666, FP32 127^3 (221 MB) 89.8 / 77.2; the same from 2 GB
+//   on (256^3 FP64 1347 / 1346); below: FP64 48^3 (24 MB) 10.3 / 11.0.
+inline bool cached_stores(bool pull, uint64_t bytes)
+{
+    constexpr uint64_t MB = 1000000;
+    if (!pull) return bytes > 36 * MB && bytes < 2000 * MB;
+    return bytes < 8 * MB || (bytes > 36 * MB && bytes <= 256 * MB);
+}
 
 // Threads of a workgroup of the step.  One wavefront for the exact stabilizer
 // (two waves per SIMD, and LDS for 64 threads: `collide`).  Otherwise 256, and
@@ -97,7 +119,7 @@ inline uint32_t step_threads(bool exact_gamma, uint32_t nnodes, uint32_t cus)
 // The kernel and launch shape launch_step uses (for building graphs of steps).
 using StepFn = void (*)(StepParams);
 hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gamma, uint32_t block,
-                             const Geom& g, StepFn* fn, uint32_t* grid);
+                             bool cached, const Geom& g, StepFn* fn, uint32_t* grid);
 
 // ---------------------------------------------------------------------------
 // Two steps of a pull box in one launch (k_pair, kbc_pair.h): a workgroup of
@@ -179,7 +201,7 @@ struct PairParams {
 };
 using PairFn = void (*)(PairParams);
 // The kernel pair_plan's boxes run (storage FP64 or FP32 dev).
-PairFn pair_step(int storage, int variant);
+PairFn pair_step(int storage, int variant, bool cached);
 
 // Write f^eq(rho, u) of device fields u [3][N], rho [N] (may be NULL) into the
 // storage buffer in the given layout.
@@ -237,7 +259,7 @@ hipError_t launch_series_sums(const Geom& g, int count, const double* runs, doub
 hipError_t launch_copy16(void* dst, const void* src, size_t n16, hipStream_t stream);
 hipError_t launch_rewrite16(void* p, size_t n16, hipStream_t stream);
 
-// Deterministic FP64 reductions over a velocity field u [3][N].
+// Sums over a velocity field u [3][N], in a fixed order.
 // *out = sum_x |curl_FD2 u(x)|^2; partial: reduce_partials().
 hipError_t launch_curl(const Geom& g, const double* u, double* partial, double* out,
                        hipStream_t stream);
@@ -319,9 +341,9 @@ using GammaFn = void (*)(int, const void*, Geom, Coll, LoadCtx, double*);
 // c64: the box is x-blocked in chunks of 64 nodes (a pull sweep may then
 // take a kernel with that geometry compiled in)
 template <int S, bool GX>
-StepFn step_kernel(int variant, int sweep, bool c64);
+StepFn step_kernel(int variant, int sweep, bool c64, bool cached);
 template <int S>
-PairFn pair_kernel(int variant);               // FP64 and FP32 dev, estimate gamma only
+PairFn pair_kernel(int variant, bool cached);               // FP64 and FP32 dev, estimate gamma only
 template <int S>
 PoolFn pool_kernel(int variant, int sweep, bool one);   // estimate gamma only
 template <int S>

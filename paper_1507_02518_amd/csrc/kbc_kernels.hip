@@ -535,7 +535,7 @@ __global__ void __launch_bounds__(kBlock) k_gamma_final(const double* __restrict
 }
 
 // Sums over the (y, z) lines of u'_c(x) u'_c(x + r) for the components c = x, y
-// and r = 0..rmax.  A workgroup stages kCorrLines lines of one component in
+// and r = 0..rmax.  A workgroup stages a few lines of one component in
 // LDS, each followed by its own start (so that x + r needs no wrap) and padded
 // by one value in eight, and splits the products into tiles of 8 nodes x 8
 // lags: 23 reads from LDS for 64 multiply-adds in registers, where one lag per
@@ -700,7 +700,7 @@ static bool chunks_of_64(const Geom& g)
 }
 
 hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gamma, uint32_t block,
-                             const Geom& g, StepFn* fn, uint32_t* grid)
+                             bool cached, const Geom& g, StepFn* fn, uint32_t* grid)
 {
     // whole waves, and the threads the kernel was compiled for
     if (block < 64 || block % 64 || block > (exact_gamma ? 64u : (uint32_t)kStepBlock)) return hipErrorInvalidValue;
@@ -708,29 +708,29 @@ hipError_t step_launch_shape(int storage, int variant, int sweep, bool exact_gam
     if (sweep != SW_PULL && !geom_is_planes(g)) return hipErrorInvalidValue;
     const bool c64 = chunks_of_64(g);
     switch (storage) {
-    case ST_F64: *fn = exact_gamma ? step_kernel<ST_F64, true>(variant, sweep, c64) : step_kernel<ST_F64, false>(variant, sweep, c64); break;
-    case ST_F32: *fn = exact_gamma ? step_kernel<ST_F32, true>(variant, sweep, c64) : step_kernel<ST_F32, false>(variant, sweep, c64); break;
-    case ST_F32X: *fn = exact_gamma ? step_kernel<ST_F32X, true>(variant, sweep, c64) : step_kernel<ST_F32X, false>(variant, sweep, c64); break;
-    default: *fn = exact_gamma ? step_kernel<ST_F16, true>(variant, sweep, c64) : step_kernel<ST_F16, false>(variant, sweep, c64); break;
+    case ST_F64: *fn = exact_gamma ? step_kernel<ST_F64, true>(variant, sweep, c64, cached) : step_kernel<ST_F64, false>(variant, sweep, c64, cached); break;
+    case ST_F32: *fn = exact_gamma ? step_kernel<ST_F32, true>(variant, sweep, c64, cached) : step_kernel<ST_F32, false>(variant, sweep, c64, cached); break;
+    case ST_F32X: *fn = exact_gamma ? step_kernel<ST_F32X, true>(variant, sweep, c64, cached) : step_kernel<ST_F32X, false>(variant, sweep, c64, cached); break;
+    default: *fn = exact_gamma ? step_kernel<ST_F16, true>(variant, sweep, c64, cached) : step_kernel<ST_F16, false>(variant, sweep, c64, cached); break;
     }
     *grid = (g.nnodes + block - 1) / block;
     return hipSuccess;
 }
 
 hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, uint32_t block,
-                       const StepParams& p, hipStream_t stream)
+                       bool cached, const StepParams& p, hipStream_t stream)
 {
     StepFn fn;
     uint32_t grid;
-    hipError_t e = step_launch_shape(storage, variant, sweep, exact_gamma, block, p.g, &fn, &grid);
+    hipError_t e = step_launch_shape(storage, variant, sweep, exact_gamma, block, cached, p.g, &fn, &grid);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fn, dim3(grid), dim3(block), 0, stream, p);
     return hipGetLastError();
 }
 
-PairFn pair_step(int storage, int variant)
+PairFn pair_step(int storage, int variant, bool cached)
 {
-    return storage == ST_F64 ? pair_kernel<ST_F64>(variant) : pair_kernel<ST_F32>(variant);
+    return storage == ST_F64 ? pair_kernel<ST_F64>(variant, cached) : pair_kernel<ST_F32>(variant, cached);
 }
 
 hipError_t launch_pool_step(int storage, int variant, int sweep, const PoolBox* boxes,
@@ -874,7 +874,7 @@ hipError_t launch_step_series(int storage, int variant, int sweep, uint32_t bloc
 {
     StepFn step;   // whose shape and chunks the series kernel takes
     uint32_t grid;
-    hipError_t e = step_launch_shape(storage, variant, sweep, false, block, p.g, &step, &grid);
+    hipError_t e = step_launch_shape(storage, variant, sweep, false, block, false, p.g, &step, &grid);
     if (e != hipSuccess) return e;
     const bool c64 = chunks_of_64(p.g);
     SeriesFn fn;

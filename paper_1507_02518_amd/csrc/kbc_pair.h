@@ -37,7 +37,8 @@ namespace {
 // kept for one, two and three planes: 9 + 18 + 27 slots.  In FP64 that is 1 KB
 // more than half of a CU's LDS, and the last v_z = +1 population is kept for
 // one plane there and in two registers after that (52 slots).
-template <int S, int V>
+// CACHED: stores through the caches (cached_stores).
+template <int S, int V, bool CACHED>
 __global__ void __launch_bounds__(kPairBlock, pair_waves(S)) k_pair(PairParams pp)
 {
     using T = typename Traits<S>::T;
@@ -169,7 +170,7 @@ __global__ void __launch_bounds__(kPairBlock, pair_waves(S)) k_pair(PairParams p
 #pragma unroll
                     for (int i = 0; i < 27; ++i) {
                         base = scalar(base);
-                        st_pop(reinterpret_cast<T*>(base + out), q[i]);
+                        st_pop<CACHED>(reinterpret_cast<T*>(base + out), q[i]);
                         base += planeb;
                     }
                 }

@@ -37,10 +37,10 @@ constexpr int kBlock = 256;
 #endif
 constexpr int kStepBlock = KBC_STEP_BLOCK;
 
-template <typename T>
+template <bool CACHED = false, typename T>
 __device__ __forceinline__ void st_pop(T* p, T v)
 {
-    if constexpr (KBC_NT_STORE && sizeof(T) >= 4) __builtin_nontemporal_store(v, p);
+    if constexpr (KBC_NT_STORE && !CACHED && sizeof(T) >= 4) __builtin_nontemporal_store(v, p);
     else *p = v;
 }
 
@@ -50,11 +50,6 @@ __device__ __forceinline__ uint32_t wrap_add(uint32_t a, int d, uint32_t n)
     if (d > 0) return a + 1 == n ? 0u : a + 1;
     if (d < 0) return a == 0 ? n - 1 : a - 1;
     return a;
-}
-
-__device__ __forceinline__ uint32_t node_of(uint32_t x, uint32_t y, uint32_t z, const Geom& g)
-{
-    return (z * g.ny + y) * g.nx + x;
 }
 
 // One node of one step: 27 gathered loads, the collision, 27 stores.
@@ -82,13 +77,16 @@ typedef __attribute__((address_space(1))) char gchar_t;
 // immediate offset field where it reaches (FP16: all 27, 128 bytes apart)
 // instead of one scalar base per direction.
 //
+// CACHED: stores through the caches (cached_stores).
+//
 // pre(f): called with the node's decoded populations before the collision.
 struct NoPre {
     template <typename R>
     __device__ __forceinline__ void operator()(R (&)[27]) const {}
 };
 
-template <int S, int V, int SW, bool GX = false, bool ALN = false, bool C64 = false, typename Pre = NoPre>
+template <int S, int V, int SW, bool GX = false, bool ALN = false, bool C64 = false,
+          bool CACHED = false, typename Pre = NoPre>
 __device__ __forceinline__ void node_update(const void* srcv, void* dstv, const Geom& g,
                                             const Coll& c, const int8_t* sexp, uint32_t n,
                                             uint32_t n0 = 0, bool store = true, Pre pre = Pre())
@@ -149,7 +147,7 @@ __device__ __forceinline__ void node_update(const void* srcv, void* dstv, const 
         else return *p;
     };
     auto st = [&](int slot, uint32_t off, T v) {
-        st_pop(reinterpret_cast<T*>(plane(dst, slot, SW != SW_AA_ODD) + off), v);
+        st_pop<CACHED>(reinterpret_cast<T*>(plane(dst, slot, SW != SW_AA_ODD) + off), v);
     };
 
     // FP16 scale exponent of direction i: the host makes it equal for i and
@@ -304,6 +302,30 @@ __device__ __forceinline__ uint32_t step_block(uint32_t b, uint32_t grid, uint32
     return b;
 }
 
+template <int S, int V, int SW, bool GX, bool C64, bool CACHED>
+__device__ __forceinline__ void step_body(const StepParams& p)
+{
+    // pairs only where a row is longer than a workgroup: the halves of a
+    // split row are what that order keeps in one L2
+    uint32_t order = SW != SW_PULL && !GX ? p.xcd_order : ORDER_PLAIN;
+    if (order == ORDER_PAIRS && p.g.nx <= blockDim.x) order = ORDER_PLAIN;
+    const uint32_t n0 = step_block(blockIdx.x, gridDim.x, order) * blockDim.x;
+    const uint32_t n = n0 + threadIdx.x;
+    // aligned stores where the exchange costs no occupancy: FP64 (2 waves
+    // per SIMD either way) and FP32 with the FP64-formed non-equilibrium (3);
+    // the plain FP32 and FP16 sweeps would drop from 4 waves to 3 (FP32 at
+    // 512^3 measured 5% slower with the exchange)
+    if constexpr (SW == SW_AA_ODD && !GX && KBC_AA_ALIGNED && (S == ST_F64 || S == ST_F32X)) {
+        // every thread reaches the workgroup barrier of the aligned stores
+        const bool real = n < p.g.nnodes;
+        node_update<S, V, SW, GX, true, false, CACHED>(p.src, p.dst, p.g, p.c, p.scale_exp,
+                                        real ? n : p.g.nnodes - 1, n0, real);
+    } else {
+        if (n >= p.g.nnodes) return;
+        node_update<S, V, SW, GX, false, C64, CACHED>(p.src, p.dst, p.g, p.c, p.scale_exp, n);
+    }
+}
+
 // Fused step of one box: one thread per node, workgroups of up to
 // kStepBlock threads (the launch picks the size).  GX: exact stabilizer,
 // which fits two waves per SIMD with one of its FP64 arrays in LDS (13.5 KB
@@ -319,25 +341,15 @@ __attribute__((amdgpu_waves_per_eu(GX ? 2 : 1, 8)))
 #endif
 k_step(StepParams p)
 {
-    // pairs only where a row is longer than a workgroup: the halves of a
-    // split row are what that order keeps in one L2
-    uint32_t order = SW != SW_PULL && !GX ? p.xcd_order : ORDER_PLAIN;
-    if (order == ORDER_PAIRS && p.g.nx <= blockDim.x) order = ORDER_PLAIN;
-    const uint32_t n0 = step_block(blockIdx.x, gridDim.x, order) * blockDim.x;
-    const uint32_t n = n0 + threadIdx.x;
-    // aligned stores where the exchange costs no occupancy: FP64 (2 waves
-    // per SIMD either way) and FP32 with the FP64-formed non-equilibrium (3);
-    // the plain FP32 and FP16 sweeps would drop from 4 waves to 3 (FP32 at
-    // 512^3 measured 5% slower with the exchange)
-    if constexpr (SW == SW_AA_ODD && !GX && KBC_AA_ALIGNED && (S == ST_F64 || S == ST_F32X)) {
-        // every thread reaches the workgroup barrier of the aligned stores
-        const bool real = n < p.g.nnodes;
-        node_update<S, V, SW, GX, true>(p.src, p.dst, p.g, p.c, p.scale_exp,
-                                        real ? n : p.g.nnodes - 1, n0, real);
-    } else {
-        if (n >= p.g.nnodes) return;
-        node_update<S, V, SW, GX, false, C64>(p.src, p.dst, p.g, p.c, p.scale_exp, n);
-    }
+    step_body<S, V, SW, GX, C64, false>(p);
+}
+
+// The same step with stores through the caches (cached_stores).
+template <int S, int V, int SW>
+__global__ void __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(1, 8)))
+k_step_cached(StepParams p)
+{
+    step_body<S, V, SW, false, false, true>(p);
 }
 
 typedef __attribute__((address_space(1))) char gchar;

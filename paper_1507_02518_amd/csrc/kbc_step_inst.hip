@@ -24,9 +24,19 @@ constexpr bool kGX = KBC_INST_EXACT != 0;
 // the same either way.
 constexpr bool kC64 = kS == ST_F16 || kGX;
 
+// FP16 stores go through the caches as they are, and the exact stabilizer is bound
+// by arithmetic.
+constexpr bool kCached = kS != ST_F16 && !kGX;
+
 template <int V>
-StepFn step_of_sweep(int sw, bool c64)
+StepFn step_of_sweep(int sw, bool c64, bool cached)
 {
+    if constexpr (kCached) {
+        if (cached) {
+            if (sw == SW_PULL) return k_step_cached<kS, V, SW_PULL>;
+            return sw == SW_AA_EVEN ? k_step_cached<kS, V, SW_AA_EVEN> : k_step_cached<kS, V, SW_AA_ODD>;
+        }
+    }
     if (sw == SW_PULL) {
         if constexpr (kC64) {
             if (c64) return k_step<kS, V, SW_PULL, kGX, true>;
@@ -60,18 +70,18 @@ PoolFn pool_of_sweep(int sw, bool one)
 }  // namespace
 
 template <int S, bool GX>
-StepFn step_kernel(int v, int sw, bool c64)
+StepFn step_kernel(int v, int sw, bool c64, bool cached)
 {
     static_assert(S == kS && GX == kGX, "instantiated for one storage form and mode only");
     switch (v) {
-    case V_D: return step_of_sweep<V_D>(sw, c64);
-    case V_DT: return step_of_sweep<V_DT>(sw, c64);
-    case V_DQ: return step_of_sweep<V_DQ>(sw, c64);
-    case V_CD: return step_of_sweep<V_CD>(sw, c64);
-    case V_CDT: return step_of_sweep<V_CDT>(sw, c64);
-    case V_CDQ: return step_of_sweep<V_CDQ>(sw, c64);
-    case V_CDTQ: return step_of_sweep<V_CDTQ>(sw, c64);
-    default: return step_of_sweep<V_DTQ>(sw, c64);
+    case V_D: return step_of_sweep<V_D>(sw, c64, cached);
+    case V_DT: return step_of_sweep<V_DT>(sw, c64, cached);
+    case V_DQ: return step_of_sweep<V_DQ>(sw, c64, cached);
+    case V_CD: return step_of_sweep<V_CD>(sw, c64, cached);
+    case V_CDT: return step_of_sweep<V_CDT>(sw, c64, cached);
+    case V_CDQ: return step_of_sweep<V_CDQ>(sw, c64, cached);
+    case V_CDTQ: return step_of_sweep<V_CDTQ>(sw, c64, cached);
+    default: return step_of_sweep<V_DTQ>(sw, c64, cached);
     }
 }
 
@@ -91,7 +101,7 @@ GammaFn gamma_kernel(int v)
     }
 }
 
-template StepFn step_kernel<kS, kGX>(int, int, bool);
+template StepFn step_kernel<kS, kGX>(int, int, bool, bool);
 template GammaFn gamma_kernel<kS, kGX>(int);
 
 #if !KBC_INST_EXACT
@@ -133,26 +143,36 @@ SeriesFn series_kernel(int v, int sw, bool c64)
 template SeriesFn series_kernel<kS>(int, int, bool);
 
 #if KBC_INST_STORAGE == 0 || KBC_INST_STORAGE == 1
+template <int V>
+PairFn pair_of(bool cached)
+{
+    // FP32 boxes that step in pairs are larger than the last-level cache
+    if constexpr (kS == ST_F64) {
+        if (cached) return k_pair<kS, V, true>;
+    }
+    return k_pair<kS, V, false>;
+}
+
 template <int S>
-PairFn pair_kernel(int v)
+PairFn pair_kernel(int v, bool cached)
 {
     static_assert(S == kS, "instantiated for one storage form only");
     switch (v) {
-    case V_D: return k_pair<kS, V_D>;
-    case V_DT: return k_pair<kS, V_DT>;
-    case V_DQ: return k_pair<kS, V_DQ>;
+    case V_D: return pair_of<V_D>(cached);
+    case V_DT: return pair_of<V_DT>(cached);
+    case V_DQ: return pair_of<V_DQ>(cached);
 #if KBC_INST_STORAGE == 0
     // pair_plan takes no FP32 box with a central variant
-    case V_CD: return k_pair<kS, V_CD>;
-    case V_CDT: return k_pair<kS, V_CDT>;
-    case V_CDQ: return k_pair<kS, V_CDQ>;
-    case V_CDTQ: return k_pair<kS, V_CDTQ>;
+    case V_CD: return pair_of<V_CD>(cached);
+    case V_CDT: return pair_of<V_CDT>(cached);
+    case V_CDQ: return pair_of<V_CDQ>(cached);
+    case V_CDTQ: return pair_of<V_CDTQ>(cached);
 #endif
-    default: return k_pair<kS, V_DTQ>;
+    default: return pair_of<V_DTQ>(cached);
     }
 }
 
-template PairFn pair_kernel<kS>(int);
+template PairFn pair_kernel<kS>(int, bool);
 #endif
 #endif
 

@@ -111,6 +111,15 @@ def test_series_is_the_energy_after_each_step(shape, n, dtype, streaming, varian
     _check_series(shape, n, dtype, streaming, variant)
 
 
+@pytest.mark.parametrize("dtype,streaming,variant", [
+    (F64, PULL, kbc.S_DTQ), (F64, AA, kbc.S_CD), (F32_DEV, PULL, kbc.S_CDTQ), (F32_DEV, AA, kbc.S_DTQ),
+    (F32_DEV_X, PULL, kbc.S_D), (F32_DEV_X, AA, kbc.S_CDT)])
+def test_steps_that_store_through_the_caches_give_the_same_bits(dtype, streaming, variant):
+    """Lattices between the L2s' and the last-level cache's size: the single
+    steps store through the caches, those of the series past them."""
+    _check_series((97, 64, 80), 5, dtype, streaming, variant)
+
+
 def test_series_with_fewer_states_at_once():
     """A box large enough that its states are added up in smaller numbers."""
     _check_series((192, 160, 132), 21, F32_DEV, AA, kbc.S_DTQ)
