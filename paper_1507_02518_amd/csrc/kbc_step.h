@@ -303,13 +303,14 @@ __device__ __forceinline__ uint32_t step_block(uint32_t b, uint32_t grid, uint32
 }
 
 template <int S, int V, int SW, bool GX, bool C64, bool CACHED>
-__device__ __forceinline__ void step_body(const StepParams& p)
+__device__ __forceinline__ void step_body(const StepParams& p, uint32_t block, uint32_t grid,
+                                          uint32_t threads)
 {
     // pairs only where a row is longer than a workgroup: the halves of a
     // split row are what that order keeps in one L2
     uint32_t order = SW != SW_PULL && !GX ? p.xcd_order : ORDER_PLAIN;
-    if (order == ORDER_PAIRS && p.g.nx <= blockDim.x) order = ORDER_PLAIN;
-    const uint32_t n0 = step_block(blockIdx.x, gridDim.x, order) * blockDim.x;
+    if (order == ORDER_PAIRS && p.g.nx <= threads) order = ORDER_PLAIN;
+    const uint32_t n0 = step_block(block, grid, order) * threads;
     const uint32_t n = n0 + threadIdx.x;
     // aligned stores where the exchange costs no occupancy: FP64 (2 waves
     // per SIMD either way) and FP32 with the FP64-formed non-equilibrium (3);
@@ -341,7 +342,7 @@ __attribute__((amdgpu_waves_per_eu(GX ? 2 : 1, 8)))
 #endif
 k_step(StepParams p)
 {
-    step_body<S, V, SW, GX, C64, false>(p);
+    step_body<S, V, SW, GX, C64, false>(p, blockIdx.x, gridDim.x, blockDim.x);
 }
 
 // The same step with stores through the caches (cached_stores).
@@ -349,7 +350,7 @@ template <int S, int V, int SW>
 __global__ void __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(1, 8)))
 k_step_cached(StepParams p)
 {
-    step_body<S, V, SW, false, false, true>(p);
+    step_body<S, V, SW, false, false, true>(p, blockIdx.x, gridDim.x, blockDim.x);
 }
 
 typedef __attribute__((address_space(1))) char gchar;
