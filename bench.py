@@ -5,8 +5,9 @@
 Workload (synthetic, seeded): a 256^3 periodic box of decaying homogeneous
 isotropic turbulence, initial spectrum E(k) ~ k^4 exp(-2 (k/k0)^2), k0 = 4,
 u_rms = 0.04, rho = 1, nu = 5e-4, populations at the product-form
-equilibrium; KBC model s = d+t+q with the entropic stabilizer.  One step is
-one launch of the fused kernel over all 16.8 M nodes.  The headline line is
+equilibrium; KBC model s = d+t+q with the entropic stabilizer.  The fused
+kernel updates all 16.8 M nodes, FP64 and natural FP32 pull boxes two steps per
+launch (k_pair), the other forms one (k_step).  The headline line is
 FP64 storage with pull streaming (the form matched element-wise to the CPU
 oracle); the other storage forms, the s = d variant, the central-moment
 default s = d~+t~+q~ and the exact stabilizer (root of the entropy condition
@@ -19,7 +20,7 @@ nu = 2.5e-4, seed 2) in FP32 / FP16 deviation storage and FP64 is timed under
 single boxes on the same inputs.
 
 Prints one JSON line with MLUPS, the roofline of the step kernel (HBM bound,
-algorithmic bytes 2 * 27 * bytes-per-population per node and step, timed with
+algorithmic bytes 2 * 27 * bytes-per-population per node and launch, timed with
 HIP events on the stream the kernel runs on), and the CPU oracle timed on a
 bounded sample of the same workload.
 """
@@ -57,26 +58,34 @@ KERNEL_SOURCES = ("kbc_device.h", "kbc_internal.h", "kbc_step.h", "kbc_step_inst
                   "kbc_kernels.hip")
 
 
-def kernel_source_digest() -> str:
+def kernel_source_digest(extra=()) -> str:
     h = hashlib.sha256()
-    for name in KERNEL_SOURCES:
+    for name in KERNEL_SOURCES + tuple(extra):
         with open(os.path.join(CSRC, name), "rb") as f:
             h.update(name.encode())
             h.update(f.read())
     return h.hexdigest()[:16]
 
 
-def read_counters():
-    """HBM bytes per step launch from the committed rocprofv3 --pmc summary,
-    or None if it is absent or was taken on different kernel sources."""
-    if not os.path.exists(COUNTERS):
+# the forms of the 256^3 box that take two steps per launch (k_pair)
+PAIR_FORMS = {("F64", "PULL", None), ("F64", "PULL", "S_D"), ("F64", "PULL", "S_CDTQ"),
+              ("F32_DEV", "PULL", None)}
+PAIR_COUNTERS = os.path.join(ROOT, "profiles", "pair_f64_pull_256_counters.txt")
+PAIR_SOURCES = ("kbc_pair.h",)
+
+
+def read_counters(path=COUNTERS, extra=()):
+    """HBM bytes per launch from the committed rocprofv3 --pmc summary of the
+    single step (of the pair: PAIR_COUNTERS, PAIR_SOURCES), or None if it is
+    absent or was taken on different kernel sources."""
+    if not os.path.exists(path):
         return None
     vals = {}
-    for line in open(COUNTERS):
+    for line in open(path):
         if "=" in line and not line.lstrip().startswith("#"):
             k, v = line.split("=", 1)
             vals[k.strip()] = v.strip()
-    if vals.get("kernel_source_digest") != kernel_source_digest():
+    if vals.get("kernel_source_digest") != kernel_source_digest(extra):
         return None
     try:
         return float(vals["hbm_bytes_per_launch"])
@@ -117,16 +126,22 @@ def valu_issue_ms(counts, storage, streaming, var, n):
     # with that geometry compiled in
     c64 = ("true" if streaming == "PULL" and n % 64 == 0 and n > 64
            and (storage == "F16_DEV" or var == "exact") else "false")
-    names = [f"k_step<{STORAGE_INDEX[storage]}, {VARIANT_INDEX[var]}, {sw}, {gx}, "
-             f"{c64 if sw == 0 else 'false'}>" for sw in sweeps]
-    if not all(nm in counts for nm in names):
-        return None
-    per_wave = sum(counts[nm] for nm in names) / len(names)
+    per_wave = 0.0
+    for sw in sweeps:
+        si, vi = STORAGE_INDEX[storage], VARIANT_INDEX[var]
+        # a box's steps store past the caches (k_step) or through them
+        for nm in (f"k_step<{si}, {vi}, {sw}, {gx}, {c64 if sw == 0 else 'false'}>",
+                   f"k_step_cached<{si}, {vi}, {sw}>"):
+            if nm in counts:
+                per_wave += counts[nm] / len(sweeps)
+                break
+        else:
+            return None
     return per_wave * (n ** 3 / 64) / VALU_ISSUE_PER_S * 1e3
 
 
 def time_form(kbc, torch, u_dev, dtype, streaming, steps, warmup, stream, variant=None,
-              gamma=None, n=N, nu=NU):
+              gamma=None, n=N, nu=NU, per_launch=1):
     # the box enqueues on `stream` (a torch stream of default priority); the
     # events are recorded on the same stream, so they bracket the launches
     variant = kbc.S_DTQ if variant is None else variant
@@ -147,8 +162,9 @@ def time_form(kbc, torch, u_dev, dtype, streaming, steps, warmup, stream, varian
         bpn = box.bytes_per_node_step()
         k = box.energy()
     mlups = n ** 3 / (ms * 1e-3) / 1e6
-    gbs = bpn * n ** 3 / (ms * 1e-3) / 1e9
-    return {"ms_per_step": ms, "mlups": mlups, "algorithmic_GBs": gbs,
+    # a launch reads and writes every population once, whatever steps it takes
+    gbs = bpn * n ** 3 / (ms * per_launch * 1e-3) / 1e9
+    return {"ms_per_step": ms, "steps_per_launch": per_launch, "mlups": mlups, "algorithmic_GBs": gbs,
             "frac_hbm_peak": gbs / PEAK_HBM_GBS, "bytes_per_node_step": bpn,
             "wall_s": wall, "energy_after": k}
 
@@ -459,7 +475,8 @@ def run_forms(kbc, torch, u_dev, table, names, steps, warmup, stream, n, nu):
             var, gamma = None, "exact"
         variant = getattr(kbc, var) if var else None
         r = time_form(kbc, torch, u_dev, getattr(kbc, dt), getattr(kbc, st), steps, warmup,
-                      stream, variant, gamma, n=n, nu=nu)
+                      stream, variant, gamma, n=n, nu=nu,
+                      per_launch=2 if n == N and (dt, st, var_name) in PAIR_FORMS else 1)
         t_valu = valu_issue_ms(counts, dt, st, var_name, n) if counts else None
         if t_valu is not None:
             r["valu_issue_ms"] = t_valu
@@ -526,7 +543,8 @@ def main():
     torch.cuda.synchronize()
 
     log("[bench] FP64 pull (headline)")
-    head = time_form(kbc, torch, u_dev, kbc.F64, kbc.PULL, args.steps, args.warmup, stream)
+    head = time_form(kbc, torch, u_dev, kbc.F64, kbc.PULL, args.steps, args.warmup, stream,
+                     per_launch=2)
     log(f"[bench]   {head['mlups']:.0f} MLUPS, {head['algorithmic_GBs']:.0f} GB/s")
 
     forms = run_forms(kbc, torch, u_dev, FORMS_256, forms_256, args.steps, args.warmup, stream,
@@ -552,7 +570,7 @@ def main():
 
     batched = ensemble_and_serving(kbc, args)
 
-    traffic_bytes = read_counters()
+    traffic_bytes = read_counters(PAIR_COUNTERS, PAIR_SOURCES)
     roofline = {
         "bound": "hbm",
         "achieved": round(head["algorithmic_GBs"], 1),
@@ -560,8 +578,11 @@ def main():
         "unit": "GB/s",
         "frac": round(head["algorithmic_GBs"] / PEAK_HBM_GBS, 4),
         "traffic": traffic_bytes,
-        "kernel": "k_step<F64, d+t+q, pull>",
-        "bytes_per_node_step": head["bytes_per_node_step"],
+        "kernel": "k_pair<F64, d+t+q>",
+        "steps_per_launch": head["steps_per_launch"],
+        "bytes_per_node_launch": head["bytes_per_node_step"],
+        # what single steps would have to move in the same time
+        "single_step_equivalent_GBs": round(head["algorithmic_GBs"] * head["steps_per_launch"], 1),
         "nodes_per_launch": N ** 3,
         "copy_ceiling_GBs": round(copy_gbs, 1),
         "frac_of_copy_ceiling": round(head["algorithmic_GBs"] / copy_gbs, 4),
