@@ -539,16 +539,21 @@ __host__ __device__ __forceinline__ bool gamma_exact_root(const double (&dh)[27]
         // expansion to k = 4 (Newton from Halley's step) is the root of G to
         // within |d| q^4 / (5 (1 - q)), q = |beta d| rmax; where that is below
         // the tolerance one pass over the populations has found gamma.
-        double d = step;
+        // A d that Newton's method has not converged to can be small by chance:
+        // its last correction has to be negligible as well (what is left is
+        // of the order of its square).
+        double d = step, last = 0.0;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const double y = beta * d;
             const double P = G - y * (M1 + y * (0.5 * M2 + y * ((1.0 / 3.0) * M3 + 0.25 * y * M4)));
             const double dP = -beta * (M1 + y * (M2 + y * (M3 + y * M4)));
-            d -= P / dP;
+            last = P / dP;
+            d -= last;
         }
         const double q = fabs(beta * d) * rmax, q2 = q * q;
-        if (q < 0.25 && fabs(d) * q2 * q2 <= 4.0 * dg_tol * (1.0 - q)) {
+        if (q < 0.25 && fabs(d) * q2 * q2 <= 4.0 * dg_tol * (1.0 - q) &&
+            fabs(beta * last) * rmax <= 1e-8) {
             const double gn = g + d;
             if (gn > lo && gn < hi) {
                 g = gn;
