@@ -135,6 +135,14 @@ __device__ inline void node_xyz(uint32_t n, const Geom& g, uint32_t& x, uint32_t
     y = yz - z * g.ny;
 }
 
+// Coordinate a - m of a periodic axis of n nodes; the reach m may exceed the
+// axis.  No multiple of n is formed: n may lie just below 2^31.
+__host__ __device__ __forceinline__ uint32_t periodic_minus(uint32_t a, uint32_t m, uint32_t n)
+{
+    const uint32_t r = a % n, s = m % n;
+    return r >= s ? r - s : r + (n - s);
+}
+
 // ---------------------------------------------------------------------------
 // Storage codecs.  F64 stores f_i; F32 stores f_i - W_i; F16 stores
 // (f_i - W_i) * scale_i rounded to nearest even.  The arithmetic type R is

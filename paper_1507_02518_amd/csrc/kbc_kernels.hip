@@ -428,13 +428,13 @@ __global__ void __launch_bounds__(kBlock) k_grad_stats(Geom g, const double* __r
 #pragma unroll
         for (uint32_t k = 0; k < PER; ++k) {
             const uint32_t e = t + k * kBlock;
-            const uint32_t x = (x0 + e % W + M * g.nx - M) % g.nx, y = (y0 + e / W + M * g.ny - M) % g.ny;
+            const uint32_t x = periodic_minus(x0 + e % W, M, g.nx), y = periodic_minus(y0 + e / W, M, g.ny);
             from[k] = y * g.nx + x;
         }
         double col[3][2 * M + 1];   // [a][d]: u_a at plane z - M + d
 #pragma unroll
         for (int d = 1; d <= 2 * M; ++d) {
-            const size_t at = (size_t)((z0 + d - 1 + M * g.nz - M) % g.nz) * slab + own;
+            const size_t at = (size_t)periodic_minus(z0 + d - 1, M, g.nz) * slab + own;
 #pragma unroll
             for (int a = 0; a < 3; ++a) col[a][d] = u[a * N + at];
         }
