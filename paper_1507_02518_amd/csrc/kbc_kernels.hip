@@ -392,18 +392,42 @@ template <> struct FdW<8> {
     }
 };
 
-// Per-block sums of |curl u|^2, sum_ab (d_a u_b + d_b u_a)^2, (div u)^2 and
-// (du_x/dx)^n for n = 2..6 (fixed order).  A workgroup marches a tile of
-// 32 x 8 columns through kGradPlanes planes: a thread keeps its column's
+// Adds a node's |curl u|^2, sum_ab (d_a u_b + d_b u_a)^2, (div u)^2 and
+// (du_x/dx)^n for n = 2..6, given G[a][b] = d u_a / d x_b.
+__device__ __forceinline__ void add_grad(const double (&G)[3][3], double (&acc)[8])
+{
+    const double wx = G[2][1] - G[1][2], wy = G[0][2] - G[2][0], wz = G[1][0] - G[0][1];
+    acc[0] += wx * wx + wy * wy + wz * wz;
+    double e = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const double sab = G[a][b] + G[b][a];
+            e += sab * sab;
+        }
+    acc[1] += e;
+    const double dv = G[0][0] + G[1][1] + G[2][2];
+    acc[2] += dv * dv;
+    const double d1 = G[0][0], d2 = d1 * d1, d3 = d2 * d1;
+    acc[3] += d2;
+    acc[4] += d3;
+    acc[5] += d2 * d2;
+    acc[6] += d3 * d2;
+    acc[7] += d3 * d3;
+}
+
+// Per-block sums of these, fixed order.  A workgroup marches a tile of
+// 32 x 8 columns through lz planes (grad_planes): a thread keeps its column's
 // 2M + 1 planes in registers for the z derivatives, and the plane's tile with
 // its halo goes through LDS for the others, 10 loads per node and plane at
 // eighth order instead of 72 with a 64-bit remainder for each neighbour.
 // 200^3, eighth order: 0.45 -> 0.18 ms.
-constexpr uint32_t kGradX = 32, kGradY = 8, kGradPlanes = 32;
 static_assert(kGradX * kGradY == kBlock, "one thread per column");
 
 template <int ORD>
-__global__ void __launch_bounds__(kBlock) k_grad_stats(Geom g, const double* __restrict__ u,
+__global__ void __launch_bounds__(kBlock) k_grad_stats(Geom g, uint32_t lz,
+                                                       const double* __restrict__ u,
                                                        double* __restrict__ partial)
 {
     constexpr int M = FdW<ORD>::M;
@@ -413,14 +437,14 @@ __global__ void __launch_bounds__(kBlock) k_grad_stats(Geom g, const double* __r
     const uint32_t t = threadIdx.x, tx = t % kGradX, ty = t / kGradX;
     const uint32_t slab = g.nx * g.ny;
     const uint32_t ntx = (g.nx + kGradX - 1) / kGradX, nty = (g.ny + kGradY - 1) / kGradY;
-    const uint32_t items = ntx * nty * ((g.nz + kGradPlanes - 1) / kGradPlanes);
+    const uint32_t items = ntx * nty * ((g.nz + lz - 1) / lz);
     double acc[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) acc[k] = 0.0;
     for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
         const uint32_t xi = it % ntx, yz = it / ntx, x0 = xi * kGradX, y0 = yz % nty * kGradY;
-        const uint32_t z0 = yz / nty * kGradPlanes;
-        const uint32_t planes = g.nz - z0 < kGradPlanes ? g.nz - z0 : kGradPlanes;
+        const uint32_t z0 = yz / nty * lz;
+        const uint32_t planes = g.nz - z0 < lz ? g.nz - z0 : lz;
         const bool real = x0 + tx < g.nx && y0 + ty < g.ny;
         const uint32_t own = ((y0 + ty) % g.ny) * g.nx + (x0 + tx) % g.nx;
         // tile element e = t + k 256 is node (x0 - M + e % W, y0 - M + e / W), periodic
@@ -472,28 +496,47 @@ __global__ void __launch_bounds__(kBlock) k_grad_stats(Geom g, const double* __r
                 G[a][2] = dz;
             }
             if (!real) continue;
-            const double wx = G[2][1] - G[1][2], wy = G[0][2] - G[2][0], wz = G[1][0] - G[0][1];
-            acc[0] += wx * wx + wy * wy + wz * wz;
-            double e = 0.0;
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    const double sab = G[a][b] + G[b][a];
-                    e += sab * sab;
-                }
-            acc[1] += e;
-            const double dv = G[0][0] + G[1][1] + G[2][2];
-            acc[2] += dv * dv;
-            const double d1 = G[0][0], d2 = d1 * d1, d3 = d2 * d1;
-            acc[3] += d2;
-            acc[4] += d3;
-            acc[5] += d2 * d2;
-            acc[6] += d3 * d2;
-            acc[7] += d3 * d3;
+            add_grad(G, acc);
         }
     }
     __syncthreads();
+    block_sum<8>(acc, partial + 8 * blockIdx.x);
+}
+
+// The same sums with one node per thread and its neighbours from the caches,
+// for boxes that leave the tiles empty or too few (grad_planes).
+template <int ORD>
+__global__ void __launch_bounds__(kBlock) k_grad_nodes(Geom g, const double* __restrict__ u,
+                                                       double* __restrict__ partial)
+{
+    constexpr int M = FdW<ORD>::M;
+    const size_t N = g.nnodes;
+    const uint32_t slab = g.nx * g.ny;
+    double acc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = 0.0;
+    for (uint32_t n = blockIdx.x * kBlock + threadIdx.x; n < g.nnodes; n += gridDim.x * kBlock) {
+        uint32_t c[3];
+        node_xyz(n, g, c[0], c[1], c[2]);
+        const uint32_t len[3] = {g.nx, g.ny, g.nz}, step[3] = {1, g.nx, slab};
+        double G[3][3];  // G[a][b] = d u_a / d x_b
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const uint32_t base = n - c[b] * step[b];
+            uint32_t up = c[b], down = c[b];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) G[a][b] = 0.0;
+#pragma unroll
+            for (int m = 1; m <= M; ++m) {
+                up = wrap_add(up, 1, len[b]);
+                down = wrap_add(down, -1, len[b]);
+                const double *pu = u + (base + up * step[b]), *pd = u + (base + down * step[b]);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) G[a][b] += FdW<ORD>::c(m) * (pu[a * N] - pd[a * N]);
+            }
+        }
+        add_grad(G, acc);
+    }
     block_sum<8>(acc, partial + 8 * blockIdx.x);
 }
 
@@ -934,11 +977,14 @@ hipError_t launch_curl(const Geom& g, const double* u, double* partial, double* 
 hipError_t launch_grad_stats(int order, const Geom& g, const double* u, double* partial,
                              double* out, hipStream_t stream)
 {
-    const uint64_t items = (uint64_t)((g.nx + kGradX - 1) / kGradX) * ((g.ny + kGradY - 1) / kGradY) *
-                           ((g.nz + kGradPlanes - 1) / kGradPlanes);
-    const unsigned blocks = (unsigned)std::min<uint64_t>(kReduceBlocks, items);
-    if (order == 8) hipLaunchKernelGGL(k_grad_stats<8>, dim3(blocks), dim3(kBlock), 0, stream, g, u, partial);
-    else hipLaunchKernelGGL(k_grad_stats<2>, dim3(blocks), dim3(kBlock), 0, stream, g, u, partial);
+    const uint32_t lz = grad_planes(g);
+    const bool nodes = lz == 0;
+    const unsigned blocks = nodes ? std::min<unsigned>(kReduceBlocks, grid_for(g.nnodes))
+                                  : (unsigned)std::min<uint64_t>(kReduceBlocks, grad_items(g, lz));
+    if (nodes && order == 8) hipLaunchKernelGGL(k_grad_nodes<8>, dim3(blocks), dim3(kBlock), 0, stream, g, u, partial);
+    else if (nodes) hipLaunchKernelGGL(k_grad_nodes<2>, dim3(blocks), dim3(kBlock), 0, stream, g, u, partial);
+    else if (order == 8) hipLaunchKernelGGL(k_grad_stats<8>, dim3(blocks), dim3(kBlock), 0, stream, g, lz, u, partial);
+    else hipLaunchKernelGGL(k_grad_stats<2>, dim3(blocks), dim3(kBlock), 0, stream, g, lz, u, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_reduce_final_k<8>, dim3(1), dim3(kBlock), 0, stream, partial, (int)blocks, out);
