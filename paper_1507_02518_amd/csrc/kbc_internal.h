@@ -261,6 +261,12 @@ hipError_t launch_rewrite16(void* p, size_t n16, hipStream_t stream);
 
 // Sums over a velocity field u [3][N], in a fixed order.
 // *out = sum_x |curl_FD2 u(x)|^2; partial: reduce_partials().
+// A thread sums a run of curl_planes() planes of one column: long runs read u the
+// least, but where a plane has few nodes a wave's runs start far apart and
+// there are few of them (us of kbc_enstrophy with 32 / 4 / 1 planes: 1 x 1 x 4,000,000
+// 424 / 255 / 256, 1 x 1 x 65,536 71 / 36 / 35, 8 x 8 x 200,000 737 / 732 / 749, 15 x
+// 17 x 60,000 893 / 876 / 897, 512^3 FP16 3241 / 3299 / 3554).
+inline uint32_t curl_planes(const Geom& g) { return g.nx * g.ny < 256 ? 4 : 32; }
 hipError_t launch_curl(const Geom& g, const double* u, double* partial, double* out,
                        hipStream_t stream);
 // The kernel and tiles of the gradient sums: planes that a tile of kGradX x

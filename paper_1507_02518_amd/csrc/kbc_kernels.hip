@@ -309,31 +309,28 @@ __global__ void __launch_bounds__(kFinalBlock) k_energy_final(const EnergySum* _
 constexpr int kReduceBlocks = 2048;
 
 // Per-block sums of |curl u|^2, second-order central differences on the
-// periodic grid.  A thread marches a column of kCurlPlanes planes and keeps
-// u_x and u_y of three planes; an item is 256 columns of such a run of planes,
-// and the workgroups of one XCD take consecutive items, so that the rows a row
+// periodic grid.  A thread marches a column of lz planes (curl_planes) and keeps
+// u_x and u_y of three planes; an item is 256 of these runs, columns first, and
+// the workgroups of one XCD take consecutive items, so that the rows a row
 // is differenced with come from its L2.  Bound by reading u: 512^3 1.17 -> 0.97
 // ms (3.2 GB) against one node per thread in the dispatch order.
-constexpr uint32_t kCurlPlanes = 32;
-
-__global__ void __launch_bounds__(kBlock) k_curl(Geom g, const double* __restrict__ u,
+__global__ void __launch_bounds__(kBlock) k_curl(Geom g, uint32_t lz, const double* __restrict__ u,
                                                  double* __restrict__ partial)
 {
     const size_t N = g.nnodes;
     const double *ux = u, *uy = u + N, *uz = u + 2 * N;
     const uint32_t slab = g.nx * g.ny;
-    const uint32_t cols = (slab + kBlock - 1) / kBlock;
-    const uint32_t items = cols * ((g.nz + kCurlPlanes - 1) / kCurlPlanes);
+    const uint32_t runs = slab * ((g.nz + lz - 1) / lz), items = (runs + kBlock - 1) / kBlock;
     // eighth of the items of this XCD (workgroup b runs on XCD b mod 8)
     const uint32_t xcds = gridDim.x < 8 ? 1 : 8;
     const uint32_t j = blockIdx.x % xcds, q = items / xcds, r = items % xcds;
     const uint32_t first = j * q + (j < r ? j : r), last = first + q + (j < r ? 1 : 0);
     double acc[1] = {0.0};
     for (uint32_t it = first + blockIdx.x / xcds; it < last; it += (gridDim.x + xcds - 1 - j) / xcds) {
-        const uint32_t c = (it % cols) * kBlock + threadIdx.x;
-        if (c >= slab) continue;
-        const uint32_t z0 = (it / cols) * kCurlPlanes;
-        const uint32_t planes = g.nz - z0 < kCurlPlanes ? g.nz - z0 : kCurlPlanes;
+        const uint32_t run = it * kBlock + threadIdx.x;
+        if (run >= runs) continue;
+        const uint32_t z0 = run / slab * lz, c = run % slab;
+        const uint32_t planes = g.nz - z0 < lz ? g.nz - z0 : lz;
         const uint32_t y = fdiv(c, g.dnx), x = c - y * g.nx;
         const uint32_t xp = x + 1 == g.nx ? c - x : c + 1, xm = x == 0 ? c + g.nx - 1 : c - 1;
         const uint32_t yp = y + 1 == g.ny ? c - y * g.nx : c + g.nx;
@@ -966,10 +963,10 @@ int reduce_partials() { return kReduceBlocks; }
 hipError_t launch_curl(const Geom& g, const double* u, double* partial, double* out,
                        hipStream_t stream)
 {
-    const uint64_t cols = ((uint64_t)g.nx * g.ny + kBlock - 1) / kBlock;
-    const uint64_t items = cols * ((g.nz + kCurlPlanes - 1) / kCurlPlanes);
-    const unsigned blocks = (unsigned)std::min<uint64_t>(kReduceBlocks, items);
-    hipLaunchKernelGGL(k_curl, dim3(blocks), dim3(kBlock), 0, stream, g, u, partial);
+    const uint32_t lz = curl_planes(g);
+    const uint64_t runs = (uint64_t)g.nx * g.ny * ((g.nz + lz - 1) / lz);
+    const unsigned blocks = (unsigned)std::min<uint64_t>(kReduceBlocks, (runs + kBlock - 1) / kBlock);
+    hipLaunchKernelGGL(k_curl, dim3(blocks), dim3(kBlock), 0, stream, g, lz, u, partial);
     hipLaunchKernelGGL(k_reduce_final_k<1>, dim3(1), dim3(kBlock), 0, stream, partial, (int)blocks, out);
     return hipGetLastError();
 }

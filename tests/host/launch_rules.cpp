@@ -1,0 +1,33 @@
+// Prints what the launch rules choose for a box: program, rule, then the
+// rule's arguments.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "kbc_internal.h"
+
+using namespace kbc;
+
+static Geom planes(char** a)
+{
+    Geom g{};
+    g.nx = atoi(a[0]);
+    g.ny = atoi(a[1]);
+    g.nz = atoi(a[2]);
+    g.nnodes = g.nx * g.ny * g.nz;
+    geom_planes(g, 0);
+    return g;
+}
+
+int main(int argc, char** argv)
+{
+    const char* rule = argc > 1 ? argv[1] : "";
+    // curl nx ny nz: planes of a run, runs
+    if (!strcmp(rule, "curl") && argc == 5) {
+        const Geom g = planes(argv + 2);
+        const uint32_t lz = curl_planes(g);
+        printf("%u %llu\n", lz, (unsigned long long)g.nx * g.ny * ((g.nz + lz - 1) / lz));
+        return 0;
+    }
+    return 2;
+}
