@@ -298,7 +298,16 @@ inline uint32_t grad_planes(const Geom& g)
 hipError_t launch_grad_stats(int order, const Geom& g, const double* u, double* partial,
                              double* out, hipStream_t stream);
 // gamma of the next collision at every node: out[4] = sum, sum of squares,
-// min, max; partial: reduce_partials() * 4.
+// min, max; partial: gamma_blocks() * 4.
+// Workgroups of it: few waves fit a SIMD with the collision's registers, and
+// further rounds of workgroups are further prologues and partial sums (us of
+// kbc_gamma_statistics with 2048 / 1024, FP64: 512 x 512 x 4 in place 78 / 74, 100^3 75 /
+// 72, 80^3 in place 55 / 52; the same from 160^3 on).
+inline uint32_t gamma_blocks(const Geom& g)
+{
+    const uint32_t b = g.nnodes / 256 + (g.nnodes % 256 != 0);
+    return b < 1024 ? b : 1024;
+}
 hipError_t launch_gamma_stats(int storage, int variant, bool exact_gamma, int layout,
                               const void* buf, const Geom& g, const Coll& c,
                               const float* inv_scale, double* partial, double* out,

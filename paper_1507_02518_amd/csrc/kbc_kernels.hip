@@ -996,7 +996,7 @@ hipError_t launch_gamma_stats(int storage, int variant, bool exact_gamma, int la
 {
     LoadCtx lc;
     for (int i = 0; i < 27; ++i) lc.inv_scale[i] = inv_scale ? inv_scale[i] : 1.0f;
-    const unsigned blocks = std::min<unsigned>(kReduceBlocks, grid_for(g.nnodes));
+    const unsigned blocks = gamma_blocks(g);
     GammaFn fn;
     switch (storage) {
     case ST_F64: fn = exact_gamma ? gamma_kernel<ST_F64, true>(variant) : gamma_kernel<ST_F64, false>(variant); break;

@@ -29,5 +29,10 @@ int main(int argc, char** argv)
         printf("%u %llu\n", lz, (unsigned long long)g.nx * g.ny * ((g.nz + lz - 1) / lz));
         return 0;
     }
+    // gamma nx ny nz: workgroups of the stabilizer statistics
+    if (!strcmp(rule, "gamma") && argc == 5) {
+        printf("%u\n", gamma_blocks(planes(argv + 2)));
+        return 0;
+    }
     return 2;
 }

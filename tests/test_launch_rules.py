@@ -33,3 +33,8 @@ def test_curl_runs_fill_the_gpu_on_thin_boxes(rule):
         lz, runs = rule("curl", *shape)
         assert lz == 4 and runs * 4 >= shape[0] * shape[1] * shape[2], shape
     assert rule("curl", 512, 512, 512)[0] == 32
+
+
+def test_stabilizer_statistics_take_few_rounds_of_workgroups(rule):
+    assert rule("gamma", 1, 1, 1) == [1] and rule("gamma", 33, 17, 65) == [143]
+    assert rule("gamma", 100, 100, 100) == [1024] and rule("gamma", 512, 512, 512) == [1024]
