@@ -492,10 +492,12 @@ __device__ __forceinline__ void block_sum(double (&acc)[K], double* out)
 
 // Per-block sums of gamma and gamma^2 and the block's min and max of the
 // stabilizer that the next step would use at each node (the collision on the
-// stored state as far as gamma; nothing is written back).
+// stored state as far as gamma; nothing is written back).  Two waves per SIMD
+// with the exact stabilizer, as in its step: left to itself the compiler takes
+// 268-284 registers, one wave (128^3, FP64 / FP32-X: 288 / 288 -> 255 / 208 us).
 template <int S, int V, bool GX>
-__global__ void __launch_bounds__(kBlock) k_gamma_stats(int layout, const void* buf, Geom g, Coll c,
-                                                        LoadCtx lc, double* __restrict__ partial)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GX ? 2 : 1, 8)))
+k_gamma_stats(int layout, const void* buf, Geom g, Coll c, LoadCtx lc, double* __restrict__ partial)
 {
     using T = typename Traits<S>::T;
     using R = typename Traits<S>::R;
