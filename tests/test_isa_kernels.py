@@ -25,3 +25,19 @@ def test_exact_stabilizer_statistics_fit_two_waves_per_simd(asm):  # noqa: F811
     for nm, m in ks.items():
         assert m[".vgpr_count"] <= 256, (nm, m[".vgpr_count"])
         assert m[".group_segment_fixed_size"] <= 80 * 1024, nm
+
+
+def test_exact_pull_sweeps_issue_their_loads_together(asm):  # noqa: F811
+    """27 population loads with no wait between them in FP16, where the scheduler
+    had placed one after each, and at most two in the other forms (it holds
+    the last few back): a wait is a whole memory latency for every node."""
+    names = re.findall(r"^(_ZN3kbc\S*k_stepILi\dELi\dELi0ELb1\S*):", asm, flags=re.M)
+    # 4 storage forms x 8 variants x (generic, 64-node chunks)
+    assert len(names) == 4 * 8 * 2
+    for nm in names:
+        i = asm.index(nm + ":")
+        lines = [ln.strip() for ln in asm[i:asm.index(".Lfunc_end", i)].split("\n")]
+        loads = [k for k, ln in enumerate(lines) if ln.startswith("global_load")]
+        assert len(loads) == 27, (nm, len(loads))
+        waits = [ln for ln in lines[:loads[-1]] if ln.startswith("s_waitcnt") and "vmcnt" in ln]
+        assert len(waits) <= (0 if "k_stepILi2E" in nm else 2), (nm, len(waits))
