@@ -160,11 +160,25 @@ constexpr uint32_t pair_waves(int storage) { return storage == ST_F64 ? 2 : 3; }
 // central 256^3 1.05x.  FP32 with the FP64-formed non-equilibrium ran 0.97x
 // at 256^3 and FP16 is bound by arithmetic, so they keep single steps, as
 // does the exact stabilizer.
+//
+// In planes (lattices of 4 GiB and more, each tile row in 27 lines far apart)
+// the lines' alignment decides.  Pairs against single steps, FP64: rows of whole
+// 64 bytes 1.05-1.34x (280^3 1.15x, 296^3 1.05x, 320^3 1.22x, 512^3 1.22x, 48 x 800 x 800
+// 1.32x; central 280 x 300 x 300 1.12x); other rows lose (276^3 0.96x, 290^3 0.87x,
+// 310^3 0.92x, 350^3 0.83x, 281 x 500 x 200 0.83x), except where every plane
+// starts at an odd node, which slows the single step as much (301^3 1.11x,
+// 285^3 1.05x, 341^3 1.00x, 395^3 1.00x, 305^3 0.96x).  FP32: rows up to 352 nodes 1.05-
+// 1.25x (352^3, 256 x 512 x 320, 96 x 700 x 700), longer ones 0.80-1.02x (384^3 0.95x,
+// 416^3 1.02x, 512^3 0.92x, 1024 x 256 x 160 0.80x).
 inline bool pair_plan(int storage, int variant, bool exact_gamma, const Geom& g, uint32_t cus,
                       PairTiles* out)
 {
     if (exact_gamma || (storage != ST_F64 && storage != ST_F32)) return false;
     if (storage == ST_F32 && (is_central(variant) || g.nx % 32)) return false;
+    if (geom_is_planes(g)) {
+        if (storage == ST_F64 && g.nx % 8 && g.nnodes % 2 == 0) return false;
+        if (storage == ST_F32 && g.nx > 352) return false;
+    }
     PairTiles p;
     p.tx = storage == ST_F64 ? 16 : 32;
     p.ty = storage == ST_F64 ? 12 : 5;

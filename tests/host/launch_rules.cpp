@@ -34,5 +34,16 @@ int main(int argc, char** argv)
         printf("%u\n", gamma_blocks(planes(argv + 2)));
         return 0;
     }
+    // pair storage variant nx ny nz: 1 where a pull box takes its steps in pairs
+    if (!strcmp(rule, "pair") && argc == 7) {
+        const int storage = atoi(argv[2]), variant = atoi(argv[3]);
+        Geom g = planes(argv + 4);
+        // x-blocked where the lattice spans less than 4 GiB
+        const double bytes = 27.0 * g.nnodes * (storage == ST_F64 ? 8 : (storage == ST_F16 ? 2 : 4));
+        if (bytes < 4294967296.0) geom_blocked(g);
+        PairTiles t;
+        printf("%d\n", pair_plan(storage, variant, false, g, 256, &t) ? 1 : 0);
+        return 0;
+    }
     return 2;
 }

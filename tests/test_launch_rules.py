@@ -38,3 +38,23 @@ def test_curl_runs_fill_the_gpu_on_thin_boxes(rule):
 def test_stabilizer_statistics_take_few_rounds_of_workgroups(rule):
     assert rule("gamma", 1, 1, 1) == [1] and rule("gamma", 33, 17, 65) == [143]
     assert rule("gamma", 100, 100, 100) == [1024] and rule("gamma", 512, 512, 512) == [1024]
+
+
+F64, F32, DTQ, CDTQ = 0, 1, 3, 7
+
+
+def test_pairs_on_planes_only_where_rows_are_aligned(rule):
+    # 4 GiB and more: single steps are faster on these
+    for shape in ((276, 276, 276), (290, 290, 290), (310, 310, 310), (350, 350, 350), (281, 500, 200),
+                  (301, 300, 300)):
+        assert rule("pair", F64, DTQ, *shape) == [0] and rule("pair", F64, CDTQ, *shape) == [0], shape
+    for shape in ((384, 384, 384), (512, 512, 512), (512, 512, 160), (1024, 256, 160)):
+        assert rule("pair", F32, DTQ, *shape) == [0], shape
+    # and pairs on these
+    for shape in ((280, 280, 280), (320, 320, 320), (512, 512, 512), (1000, 200, 200), (301, 301, 301)):
+        assert rule("pair", F64, DTQ, *shape) == [1], shape
+    for shape in ((352, 352, 352), (256, 512, 320), (96, 700, 700)):
+        assert rule("pair", F32, DTQ, *shape) == [1], shape
+    # below 4 GiB the rows' alignment does not matter
+    for shape in ((256, 256, 256), (250, 250, 250), (97, 256, 256), (64, 64, 64)):
+        assert rule("pair", F64, DTQ, *shape) == [1], shape
