@@ -140,9 +140,8 @@ constexpr uint32_t pair_waves(int storage) { return storage == ST_F64 ? 2 : 3; }
 
 // Whether a pull box takes its steps in pairs, and with which tiles.
 //
-// A tile row is one 128-byte line: narrower or unaligned rows make the
-// non-temporal stores partial lines, and the sweep runs 1.6-2.3x slower
-// (tiles 18, 20, 22 or 30 wide at 256^3).  16 x 12 in FP64 keeps 192 of the
+// A tile row is one 128-byte line: tiles 18, 20, 22 or 30 wide, whose
+// non-temporal stores are partial lines, ran 1.6-2.3x slower at 256^3.  16 x 12 in FP64 keeps 192 of the
 // 252 nodes computed per plane.
 //
 // lz minimises plane iterations of the whole GPU, measured as rounds of
@@ -152,14 +151,16 @@ constexpr uint32_t pair_waves(int storage) { return storage == ST_F64 ? 2 : 3; }
 // the measured lz or within 2% of it, except 6% at 240.
 //
 // `fill` is the share of the plane iterations' node capacity that the box
-// uses.  FP64, natural s, pairs against single steps: 48^3 (0.33) 0.87x,
-// 64^3 (0.44) 1.18x, 80^3 (0.65) 1.13x, 128^3 (0.76) 1.20x, 256^3 (0.88)
-// 1.45x; central s, whose extra arithmetic is no longer hidden, 128^3 1.09x,
-// 256^3 1.31x.  FP32 (32 x 5 tiles, more of the sweep is arithmetic):
-// 128^3 (0.66) 1.00x, 160^3 (0.76) 1.10x, 192^3 1.12x, 256^3 (0.86) 1.26x;
-// central 256^3 1.05x.  FP32 with the FP64-formed non-equilibrium ran 0.97x
-// at 256^3 and FP16 is bound by arithmetic, so they keep single steps, as
-// does the exact stabilizer.
+// uses.  Pairs against single steps, both storing as cached_stores has it;
+// FP64, natural s: 48^3 (0.33) 0.87x, 64^3 (0.44) 1.00x, 60^3-63^3 1.04-1.20x, 80^3 (0.65)
+// 1.31x, 128^3 (0.76) 1.20x, 256^3 (0.88) 1.45x, 25 boxes of 150,000 to 1.5 million
+// nodes between 16 and 256 an axis 1.07-1.46x; central s, whose extra arithmetic is
+// no longer hidden, 128^3 1.14x, 256^3 1.31x.  FP32 (32 x 5 tiles, more of the sweep
+// is arithmetic): 128^3 1.08x, 160^3 (0.76) 1.10x, 192^3 1.12x, 256^3 (0.86) 1.26x; central
+// 256^3 1.05x; flat boxes whose single steps store through the caches 0.95-1.02x
+// (96 x 96 x 128 44.1 against 42.0 us, 256 x 240 x 12 26.7 / 25.7).  FP32 with the
+// FP64-formed non-equilibrium ran 0.97x at 256^3 and FP16 is bound by arithmetic,
+// so they keep single steps, as does the exact stabilizer.
 //
 // In planes (lattices of 4 GiB and more, each tile row in 27 lines far apart)
 // the lines' alignment decides.  Pairs against single steps, FP64: rows of whole
@@ -179,6 +180,7 @@ inline bool pair_plan(int storage, int variant, bool exact_gamma, const Geom& g,
         if (storage == ST_F64 && g.nx % 8 && g.nnodes % 2 == 0) return false;
         if (storage == ST_F32 && g.nx > 352) return false;
     }
+    if (storage == ST_F32 && cached_stores(true, 2 * geom_extent(g) * sizeof(float))) return false;
     PairTiles p;
     p.tx = storage == ST_F64 ? 16 : 32;
     p.ty = storage == ST_F64 ? 12 : 5;

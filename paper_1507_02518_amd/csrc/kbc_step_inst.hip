@@ -146,7 +146,7 @@ template SeriesFn series_kernel<kS>(int, int, bool);
 template <int V>
 PairFn pair_of(bool cached)
 {
-    // FP32 boxes that step in pairs are larger than the last-level cache
+    // pair_plan takes no FP32 box whose steps store through the caches
     if constexpr (kS == ST_F64) {
         if (cached) return k_pair<kS, V, true>;
     }

@@ -58,3 +58,11 @@ def test_pairs_on_planes_only_where_rows_are_aligned(rule):
     # below 4 GiB the rows' alignment does not matter
     for shape in ((256, 256, 256), (250, 250, 250), (97, 256, 256), (64, 64, 64)):
         assert rule("pair", F64, DTQ, *shape) == [1], shape
+
+
+def test_no_fp32_pairs_in_the_last_level_cache(rule):
+    # single steps through the caches are as fast or faster
+    for shape in ((96, 96, 128), (256, 240, 12), (256, 480, 6), (512, 240, 6), (256, 480, 8)):
+        assert rule("pair", F32, DTQ, *shape) == [0], shape
+    for shape in ((160, 160, 160), (512, 512, 16), (96, 200, 200)):
+        assert rule("pair", F32, DTQ, *shape) == [1], shape
