@@ -532,7 +532,8 @@ int kbc_create(const int64_t shape[3], double nu, int32_t dtype, const kbc_optio
     }
     const size_t bytes = geom_extent(h->g) * elem_bytes(dtype);
     const int nbuf = h->streaming == KBC_PULL ? 2 : 1;
-    h->cached = cached_stores(h->streaming == KBC_PULL, nbuf * bytes);
+    h->cached = cached_stores(h->streaming == KBC_PULL, nbuf * bytes, h->g.plane * elem_bytes(dtype),
+                              dtype == KBC_F64);
     for (int b = 0; b < nbuf; ++b) {
         e = hipMalloc(&h->buf[b], bytes);
         if (e != hipSuccess) {

@@ -95,10 +95,20 @@ hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, ui
 //   AA, more than the L2s: FP64 80^3 (110 MB) 44.2 / 39.8, 100^3 72.6 / 68.3,
 //   200^3 (1.7 GB) 705 / 666, FP32 127^3 (221 MB) 89.8 / 77.2; the same from 2 GB
 //   on (256^3 FP64 1347 / 1346); below: FP64 48^3 (24 MB) 10.3 / 11.0.
-inline bool cached_stores(bool pull, uint64_t bytes)
+//   AA, planes of exactly 16 MiB (453 MB), and of 32 MiB in FP64: the lines that the 27
+//   planes have in the caches at a time fall on the same sets, and stores past them
+//   are faster (over several allocations, FP64 128^3 178 / 179-190, 64 x 128 x 256 177-181 /
+//   178-192, 512 x 64 x 64 174-187 / 181-199, 256 x 256 x 64 332 / 339, FP32-X 512 x 64 x 128
+//   172-188 / 184-188; 160 x 128 x 128, planes of 20 MiB, 229 / 223, 192 x 128 x 128, of 24,
+//   275 / 261; 128 x 128 x 64, of 8, fits the last-level cache: 90 / 71).
+// plane_bytes: one direction plane of an AA box.
+inline bool cached_stores(bool pull, uint64_t bytes, uint64_t plane_bytes, bool f64)
 {
-    constexpr uint64_t MB = 1000000;
-    if (!pull) return bytes > 36 * MB && bytes < 2000 * MB;
+    constexpr uint64_t MB = 1000000, MiB = 1 << 20;
+    if (!pull) {
+        if (plane_bytes == 16 * MiB || (f64 && plane_bytes == 32 * MiB)) return false;
+        return bytes > 36 * MB && bytes < 2000 * MB;
+    }
     return bytes < 8 * MB || (bytes > 36 * MB && bytes <= 256 * MB);
 }
 
@@ -180,7 +190,7 @@ inline bool pair_plan(int storage, int variant, bool exact_gamma, const Geom& g,
         if (storage == ST_F64 && g.nx % 8 && g.nnodes % 2 == 0) return false;
         if (storage == ST_F32 && g.nx > 352) return false;
     }
-    if (storage == ST_F32 && cached_stores(true, 2 * geom_extent(g) * sizeof(float))) return false;
+    if (storage == ST_F32 && cached_stores(true, 2 * geom_extent(g) * sizeof(float), 0, false)) return false;
     PairTiles p;
     p.tx = storage == ST_F64 ? 16 : 32;
     p.ty = storage == ST_F64 ? 12 : 5;

@@ -45,5 +45,13 @@ int main(int argc, char** argv)
         printf("%d\n", pair_plan(storage, variant, false, g, 256, &t) ? 1 : 0);
         return 0;
     }
+    // aa storage nx ny nz: 1 where an in-place box stores through the caches
+    if (!strcmp(rule, "aa") && argc == 6) {
+        const Geom g = planes(argv + 3);
+        const bool f64 = atoi(argv[2]) == ST_F64;
+        const uint64_t plane = g.plane * (f64 ? 8 : 4);
+        printf("%d\n", cached_stores(false, 27 * plane, plane, f64) ? 1 : 0);
+        return 0;
+    }
     return 2;
 }

@@ -66,3 +66,15 @@ def test_no_fp32_pairs_in_the_last_level_cache(rule):
         assert rule("pair", F32, DTQ, *shape) == [0], shape
     for shape in ((160, 160, 160), (512, 512, 16), (96, 200, 200)):
         assert rule("pair", F32, DTQ, *shape) == [1], shape
+
+
+def test_in_place_planes_that_share_cache_sets_store_past_the_caches(rule):
+    for shape in ((128, 128, 128), (512, 64, 64), (64, 128, 256), (256, 256, 64)):
+        assert rule("aa", F64, *shape) == [0], shape
+    for shape in ((512, 64, 128), (256, 128, 128)):
+        assert rule("aa", F32, *shape) == [0], shape
+    # through them: other planes above the last-level cache, and those within it
+    for shape in ((127, 127, 127), (160, 128, 128), (192, 128, 128), (200, 200, 200), (128, 128, 64),
+                  (100, 100, 100)):
+        assert rule("aa", F64, *shape) == [1], shape
+    assert rule("aa", F32, 128, 128, 128) == [1] and rule("aa", F32, 256, 256, 128) == [1]
