@@ -523,23 +523,36 @@ int kbc_create(const int64_t shape[3], double nu, int32_t dtype, const kbc_optio
     // are padded to whole 128-byte lines, where that costs at most an eighth
     // more memory (100^3: 76.6 -> 71.0 us per step in pairs, 86 in single
     // steps).
+    bool padded = false;
     if (opt.streaming == KBC_PULL) {
         h->pairs = pair_plan(dtype, opt.variant, h->exact_gamma, h->g, (uint32_t)cus, &h->tiles);
         const uint32_t pad = (16 - h->g.nx % 16) % 16;
         if (h->pairs && dtype == KBC_F64 && !geom_is_planes(h->g) && pad > 0 && 8 * pad <= h->g.nx &&
-            27.0 * (double)(h->g.nx + pad) * h->g.ny * h->g.nz * 8.0 < 4294967296.0)
+            27.0 * (double)(h->g.nx + pad) * h->g.ny * h->g.nz * 8.0 < 4294967296.0) {
             geom_blocked16(h->g);
+            padded = true;
+        }
     }
-    const size_t bytes = geom_extent(h->g) * elem_bytes(dtype);
     const int nbuf = h->streaming == KBC_PULL ? 2 : 1;
-    h->cached = cached_stores(h->streaming == KBC_PULL, nbuf * bytes, h->g.plane * elem_bytes(dtype),
-                              dtype == KBC_F64);
-    for (int b = 0; b < nbuf; ++b) {
-        e = hipMalloc(&h->buf[b], bytes);
-        if (e != hipSuccess) {
+    for (;;) {
+        const size_t bytes = geom_extent(h->g) * elem_bytes(dtype);
+        h->cached = cached_stores(h->streaming == KBC_PULL, nbuf * bytes, h->g.plane * elem_bytes(dtype),
+                                  dtype == KBC_F64);
+        for (int b = 0; b < nbuf && e == hipSuccess; ++b) e = hipMalloc(&h->buf[b], bytes);
+        if (e == hipSuccess) break;
+        for (void*& p : h->buf) {
+            if (p) (void)hipFree(p);
+            p = nullptr;
+        }
+        // rows are padded for speed alone: without the padding the box may fit
+        if (!padded || e != hipErrorOutOfMemory) {
             kbc_destroy(h);
             return hip_fail(e, "hipMalloc(populations)");
         }
+        padded = false;
+        geom_blocked(h->g);
+        (void)hipGetLastError();
+        e = hipSuccess;
     }
     *out = h;
     return KBC_OK;

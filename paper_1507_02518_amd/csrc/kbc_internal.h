@@ -95,9 +95,9 @@ hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, ui
 //   AA, more than the L2s: FP64 80^3 (110 MB) 44.2 / 39.8, 100^3 72.6 / 68.3,
 //   200^3 (1.7 GB) 705 / 666, FP32 127^3 (221 MB) 89.8 / 77.2; the same from 2 GB
 //   on (256^3 FP64 1347 / 1346); below: FP64 48^3 (24 MB) 10.3 / 11.0.
-//   AA, planes of exactly 16 MiB (453 MB), and of 32 MiB in FP64: the lines that the 27
-//   planes have in the caches at a time fall on the same sets, and stores past them
-//   are faster (over several allocations, FP64 128^3 178 / 179-190, 64 x 128 x 256 177-181 /
+//   AA, planes of exactly 16 MiB (453 MB), and of 32 MiB in FP64: stores past the caches
+//   are faster, probably because the lines of 27 planes a power of two apart
+//   compete for the same sets (over several allocations, FP64 128^3 178 / 179-190, 64 x 128 x 256 177-181 /
 //   178-192, 512 x 64 x 64 174-187 / 181-199, 256 x 256 x 64 332 / 339, FP32-X 512 x 64 x 128
 //   172-188 / 184-188; 160 x 128 x 128, planes of 20 MiB, 229 / 223, 192 x 128 x 128, of 24,
 //   275 / 261; 128 x 128 x 64, of 8, fits the last-level cache: 90 / 71).
