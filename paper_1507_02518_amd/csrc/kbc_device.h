@@ -331,8 +331,7 @@ __host__ __device__ __forceinline__ void recip3(const R (&e)[3], R (&ie)[3])
 // of x.  The dropped Chebyshev coefficients sum to 1.7e-16, so the relative
 // error of x P(x) evaluated in FP64 stays below 4e-16 there (about two ulp,
 // as the library function): four fused multiply-adds fewer than the plain
-// Taylor series of the same accuracy.  log1p_ takes the library log1p
-// elsewhere.
+// Taylor series of the same accuracy.
 __host__ __device__ __forceinline__ double log1p_series(double x)
 {
     constexpr double c[10] = {0x1.0000000000001p+0,  -0x1.0000000000007p-1,
@@ -347,11 +346,6 @@ __host__ __device__ __forceinline__ double log1p_series(double x)
 }
 
 __host__ __device__ __forceinline__ bool log1p_series_ok(double x) { return fabs(x) < 0.0625; }
-
-__host__ __device__ __forceinline__ double log1p_(double x)
-{
-    return log1p_series_ok(x) ? log1p_series(x) : log1p(x);
-}
 
 // The same construction for wider intervals: degree 12 on |x| <= 1/8 (dropped
 // coefficients 3.6e-17) and 16 on |x| <= 1/4 (7.4e-17).
@@ -398,9 +392,10 @@ __host__ __device__ __forceinline__ double rcp_refined_(double x)
 #endif
 }
 
-// ln(1 + x) for any x > -1, to about 2e-16 absolute (the rounding of 1 + x
-// included; the stabilizer's sums need no relative accuracy near zero, where
-// the polynomials above serve): 1 + x = 2^k m with m in [1/sqrt 2, sqrt 2),
+// ln(1 + x) for any x > -1, within 3e-16 (1 + |ln(1 + x)|) of it: near zero the
+// rounding of 1 + x leaves no relative accuracy, where the polynomials above serve,
+// and the stabilizer's sums need none (an error e of ln(1 + x_i) counts as one of e
+// f'_i in a population).  1 + x = 2^k m with m in [1/sqrt 2, sqrt 2),
 // ln m = 2 atanh t, t = (m - 1)/(m + 1), and atanh t = t + t^3 P(t^2) with P the
 // degree-6 Chebyshev economization of its Taylor series on t^2 <= 0.02944
 // (dropped coefficients 1.6e-16, scaled by 2 t^3 <= 0.011).

@@ -1,5 +1,6 @@
-"""The general search of the exact stabilizer on the CPU: states 20-30% from
-equilibrium, against the oracle's bisection."""
+"""The exact stabilizer away from equilibrium, on the CPU: its general search over
+states 20-30% from equilibrium, against the oracle's bisection, and the
+logarithm it uses there."""
 import os
 import subprocess
 import tempfile
@@ -26,4 +27,19 @@ def test_no_state_far_from_equilibrium_gets_a_wrong_root(orc):
                         "-L", odir, "-lkbc_oracle", f"-Wl,-rpath,{odir}", "-lpthread", "-o", exe],
                        check=True, capture_output=True)
         r = subprocess.run([exe, "400000", "1e-9"], capture_output=True, text=True)
+        assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_logarithm_for_any_argument():
+    """Within 3e-16 (1 + |ln(1 + x)|): half an ulp of 1 + x (1.1e-16 in ln), one rounding
+    each of 2 t, the quotient t and the result (below 1.1e-16 of 0.35 or of the
+    result), k ln 2 within 2^-54 of itself, truncation below 2e-18."""
+    if not os.path.exists(CLANG):
+        pytest.skip("ROCm clang++ not present")
+    with tempfile.TemporaryDirectory() as d:
+        exe = os.path.join(d, "ln")
+        subprocess.run([CLANG, "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                        "-I", CSRC, os.path.join(ROOT, "tests", "host", "log1p_any_check.cpp"), "-o", exe],
+                       check=True, capture_output=True)
+        r = subprocess.run([exe, "3e-16"], capture_output=True, text=True)
         assert r.returncode == 0, r.stdout + r.stderr
