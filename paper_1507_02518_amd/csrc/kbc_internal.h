@@ -297,14 +297,17 @@ hipError_t launch_curl(const Geom& g, const double* u, double* partial, double* 
                        hipStream_t stream);
 // The kernel and tiles of the gradient sums: planes that a tile of kGradX x
 // kGradY columns is marched through, 0 for one node per thread.  A march is a
-// chain of plane loads, so few of them leave the GPU idle (us of
-// kbc_statistics at second / eighth order, 32-plane marches, 8-plane marches, nodes:
-// 32^3 67 / 89, 46 / 51, 38 / 42; 64^3 81 / 102, 56 / 62, 51 / 59; 96^3 102 / 125, 81 /
-// 90, 80 / 105; 128^3 188 / 211, 172 / 189, 168 / 224; 200^3 488 / 589, 507 / 568, 536 /
-// 822), and a short row or few rows leave lanes without a node (4 x 512 x 512, an
-// eighth of the lanes filled: 122 / 158, 128 / 170, 89 / 114; 8 x 1024 x 1024, a
-// quarter: 625 / 767, 636 / 800, 512 / 722; 16 x 400 x 400, half: 201 / 228, 189 / 221,
-// 187 / 259; 1 x 1 x 4,000,000: 4.3 / 6.1 ms against 0.26 / 0.36).
+// chain of plane loads: long ones leave the GPU idle on small boxes and their
+// last round of workgroups unfilled on larger ones, short ones load their first
+// planes for little (us of kbc_statistics at second / eighth order, marches of 32, 16 and
+// 8 planes, nodes: 32^3 67 / 89, 53 / 64, 46 / 51, 38 / 42; 64^3 81 / 102, 64 / 75, 56 /
+// 62, 51 / 59; 96^3 102 / 125, 86 / 99, 81 / 90, 80 / 105; 128^3 180 / 203, 166 / 185, 166 /
+// 184, 168 / 224; 200^3 491 / 593, 508 / 569, 511 / 571, 536 / 822; 256^3 982 / 1038, 982 /
+// 1051, 991 / 1064).  A short row or few rows leave lanes without a node
+// (4 x 512 x 512, an eighth of the lanes filled: 122 / 158 in marches of 32, 128 / 170 of 8,
+// 89 / 114 by nodes; 8 x 1024 x 1024, a quarter: 625 / 767, 636 / 800, 512 / 722; 16 x 400 x
+// 400, half: 201 / 228, 189 / 221, 187 / 259; 1 x 1 x 4,000,000: 4.3 / 6.1, 4.7 / 7.3, 0.26 /
+// 0.36 ms).
 constexpr uint32_t kGradX = 32, kGradY = 8;
 inline uint64_t grad_items(const Geom& g, uint32_t lz)
 {
@@ -314,9 +317,7 @@ inline uint32_t grad_planes(const Geom& g)
 {
     const double lanes = (double)grad_items(g, 1) * (kGradX * kGradY);
     if (g.nnodes <= 1u << 18 || g.nnodes < 0.4 * lanes) return 0;
-    uint32_t lz = 32;
-    while (lz > 8 && grad_items(g, lz) < 1024) lz /= 2;
-    return lz;
+    return grad_items(g, 16) < 512 ? 8 : 16;
 }
 // Flow statistics.  grad: out[8] = sums over nodes of |curl u|^2,
 // sum_ab (d_a u_b + d_b u_a)^2, (div u)^2, (du_x/dx)^n for n = 2..6, with the

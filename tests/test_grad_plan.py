@@ -36,7 +36,7 @@ def test_small_and_thin_boxes_fill_the_gpu():
         for shape in ((65, 65, 64), (80, 80, 80), (131, 97, 61), (128, 128, 128), (16, 400, 400)):
             lz, items = plan(*shape)
             assert lz in (8, 16) and items >= 200, (shape, lz, items)
-        assert plan(200, 200, 200)[0] == 32 and plan(512, 512, 512)[0] == 32
+        assert plan(200, 200, 200)[0] == 16 and plan(512, 512, 512)[0] == 16
 
 
 @pytest.mark.gpu
