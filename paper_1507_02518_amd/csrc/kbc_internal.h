@@ -94,7 +94,8 @@ hipError_t launch_step(int storage, int variant, int sweep, bool exact_gamma, ui
 //   far below it: FP64 16^3 4.20 / 3.95, FP32 24^3 (3 MB) 4.47 / 4.14.
 //   AA, more than the L2s: FP64 80^3 (110 MB) 44.2 / 39.8, 100^3 72.6 / 68.3,
 //   200^3 (1.7 GB) 705 / 666, FP32 127^3 (221 MB) 89.8 / 77.2; the same from 2 GB
-//   on (256^3 FP64 1347 / 1346); below: FP64 48^3 (24 MB) 10.3 / 11.0.
+//   on (256^3 FP64 1347 / 1346); below: FP64 48^3 (24 MB) 10.3 / 11.0, 56^3 (38 MB) 15.7 /
+//   16.1, 60^3 (47 MB) 18.8 / 19.2, while FP32 gains from there (72^3, 40 MB, 16.9 / 16.2).
 //   AA, planes of exactly 16 MiB (453 MB), and of 32 MiB in FP64: stores past the caches
 //   are faster, probably because the lines of 27 planes a power of two apart
 //   compete for the same sets (over several allocations, FP64 128^3 178 / 179-190, 64 x 128 x 256 177-181 /
@@ -107,7 +108,7 @@ inline bool cached_stores(bool pull, uint64_t bytes, uint64_t plane_bytes, bool 
     constexpr uint64_t MB = 1000000, MiB = 1 << 20;
     if (!pull) {
         if (plane_bytes == 16 * MiB || (f64 && plane_bytes == 32 * MiB)) return false;
-        return bytes > 36 * MB && bytes < 2000 * MB;
+        return bytes > (f64 ? 50 : 36) * MB && bytes < 2000 * MB;
     }
     return bytes < 8 * MB || (bytes > 36 * MB && bytes <= 256 * MB);
 }

@@ -78,3 +78,8 @@ def test_in_place_planes_that_share_cache_sets_store_past_the_caches(rule):
                   (100, 100, 100)):
         assert rule("aa", F64, *shape) == [1], shape
     assert rule("aa", F32, 128, 128, 128) == [1] and rule("aa", F32, 256, 256, 128) == [1]
+
+
+def test_in_place_fp64_boxes_little_above_the_l2s_store_past_the_caches(rule):
+    assert rule("aa", F64, 56, 56, 56) == [0] and rule("aa", F64, 60, 60, 60) == [0]
+    assert rule("aa", F64, 64, 64, 64) == [1] and rule("aa", F32, 72, 72, 72) == [1]
