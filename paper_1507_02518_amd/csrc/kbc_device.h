@@ -604,6 +604,14 @@ __host__ __device__ __forceinline__ bool gamma_exact_root(const double (&dh)[27]
 // u_rms 0.004, 256^3 2.18 -> 1.87 (FP32-X 2.07 -> 1.58), 32^3 0.036 -> 0.018.
 // Two FP64 arrays instead of three (1/f^eq_i is a product of two of twelve
 // values), one of them in LDS, let two waves share a SIMD.
+//
+// r_i takes a reciprocal of one Newton step (about 2^-46) and whole waves take
+// log1p_any for one node with |x_i| >= 1/4: r_i enters the step alone, whose remainder
+// the tolerance bounds, and neither moves the result.  Populations after one collision
+// against the oracle's bisection, 20,000 states each, rms and worst difference, on
+// the host with the device's reciprocal imitated: 5.8e-17 and 2.5e-15 for perturbations
+// of 1e-4 to 15%, 9.0e-17 and 2.4e-14 for 20%, to three digits the same as with two
+// Newton steps and as with the library's log1p.
 template <typename EFn, typename WFn, typename RefreshFn>
 __host__ __device__ __forceinline__ bool gamma_exact_fast(const double (&dh)[27], EFn ee_of,
                                                           WFn w_of, RefreshFn refresh,
