@@ -114,7 +114,8 @@ void kbc_options_default(kbc_options* opt);
  * kbc_init_velocity or kbc_set_populations.  On success *out owns the box.
  * The device layout of the populations is internal (x-blocked for pull boxes
  * whose lattice spans less than 4 GiB, with rows padded to 16 nodes in some
- * FP64 boxes, at most an eighth more; one plane per direction otherwise)
+ * FP64 boxes, at most an eighth more and only where that can be allocated; one
+ * plane per direction otherwise)
  * and never crosses this interface.  Some calls add device buffers on their
  * first use, kept until kbc_destroy: the velocity field the diagnostics
  * reduce over (24 B per node; 8 B more per node for a density that is read
@@ -142,7 +143,7 @@ int kbc_init_velocity_device(kbc_handle h, const double* u_dev, const double* rh
 /* Enqueue n >= 0 steps on the box's stream and return; t advances by n.
  * Each step is one kernel launch, or each two steps where a pull box is large
  * enough for that to be faster (FP64 from about 64^3 nodes, FP32 dev from
- * about 160^3; the same bits as two single steps); from n >= 16 on, runs of
+ * about 160^3; lattices of 4 GiB and more only with suitable rows; the same bits as two single steps); from n >= 16 on, runs of
  * 16 steps are replayed from a graph the box builds on first use (the same
  * kernels and arguments, so the same results as the launches). */
 int kbc_step(kbc_handle h, int64_t n);
